@@ -171,10 +171,9 @@ void launch_scalars(xfft_problem *p, int op, int crit, int nrhs, int parity, dou
     if (op == SC_INIT_SIGMA || op == SC_ALPHA || op == SC_SUM_ONLY) {
         A.s0 = L.fe0;
         A.n = L.fe_n;
-        // irregular-voxel slots of the kernel the last operator launch used
-        // (moment form: before the enriched ones; cached matrices: after them)
-        A.s1 = p->last_op_vm ? L.enr0 : L.cut0;
-        A.n1 = p->last_op_vm ? L.enr_n + L.vm_n : L.cut_n + L.enr_n;
+        // enriched slots, then those of the irregular-voxel kernel the last launch used
+        A.s1 = L.enr0;
+        A.n1 = L.enr_n + (p->last_op_vm ? L.vm_n : L.cut_n);
     } else {
         A.s0 = L.grn0;
         A.n = fp64 ? green_blocks<double>(p) : green_blocks<float>(p);

@@ -116,10 +116,10 @@ template <typename T> struct Tables {
     // Tables of the irregular voxels are stored with the voxel index fastest
     // ([row][nirr]), so that the lanes of a wave access consecutive words.
     T *irr_L = nullptr;      // [8][nirr] snapped corner level set of irregular voxels
-    // [6][10][nirr] moments of the smaller side of each cut Kuhn tet of the
-    // irregular voxels (upper triangle; the sign bit of entry 0 marks the - side),
-    // computed in FP64 and rounded once
-    T *irr_M = nullptr;
+    // [10][cut elements] moments of the smaller side of every cut element, in
+    // the order of tet_cut (upper triangle; the sign bit of entry 0 marks the
+    // - side), computed in FP64 and rounded once
+    T *cut_M = nullptr;
     cpx<T> *tw[3] = {nullptr, nullptr, nullptr};   // twiddles exp(-2 pi i t / n_axis)
     cpx<T> *tws[3] = {nullptr, nullptr, nullptr};  // stage-major twiddles of the compile-time LDS FFT
     T *half[3] = {nullptr, nullptr, nullptr};      // [n_axis][2]: sin, cos of pi k / n_axis
@@ -131,13 +131,12 @@ template <typename T> struct Work {
     T *u = nullptr, *f = nullptr, *d = nullptr, *z = nullptr;          // [cap][3][N]
     T *ue = nullptr, *fe = nullptr, *de = nullptr, *ze = nullptr;      // [cap][3][nX]
     cpx<T> *spec = nullptr;                                            // [cap][3][n2][n1][nh]
-    // [cap][2][cut_rows(nirr) / 64][6][64][4]: FE, then scaled enriched corner
-    // forces of the irregular voxels, 24 values (corner-major, xyz) per voxel in
-    // groups of 64 voxels, four values per row (see cut_index in operator.hip)
+    // [cap][2][cut_rows(nirr)][24]: FE, then scaled enriched corner forces of the
+    // irregular voxels (corner-major, xyz; see cut_index in op_common.h)
     T *cutbuf = nullptr;
 };
 
-// irregular voxels rounded up to whole groups of 64 (corner-force buffer)
+// irregular voxels rounded up to a multiple of 64 (corner-force buffer)
 __host__ __device__ inline int64_t cut_rows(int64_t nirr) { return (nirr + 63) & ~(int64_t)63; }
 
 // Cached voxel matrices (Sec. 3, caching strategy): per irregular voxel the
@@ -153,13 +152,15 @@ constexpr int VM_GRID = 4096;     // most workgroups of a launch (each walks a c
 constexpr int VM_MAXR = 6;        // loads per launch of the cached-matrix kernel
 __host__ __device__ constexpr int vm_row(int a) { return 47 * a - a * (a - 1) / 2; }
 
+constexpr int IRR_VB = 42;        // irregular voxels per workgroup of the moment form (irregular.hip)
+
 // Partial-sum slot layout per right-hand side.
 struct SlotLayout {
     int fe0, fe_n;      // regular-voxel operator blocks at the current depth kz
     int fe_cap;         // slots reserved for the regular-voxel blocks (depth 4)
-    int cut0, cut_n;    // irregular-voxel blocks (moment form)
     int enr0, enr_n;    // enriched gather blocks
-    int vm0, vm_n;      // irregular-voxel blocks of the cached voxel matrices (right after the enriched ones)
+    int cut0, cut_n;    // irregular-voxel blocks (moment form), right after the enriched ones
+    int vm0, vm_n;      // irregular-voxel blocks of the cached voxel matrices (the same slots)
     int grn0, grn_n;    // Green (z pass) blocks
     int eu0, eu_n;      // enriched residual blocks
     int total;
@@ -217,6 +218,13 @@ struct xfft_problem {
     int32_t *irr = nullptr;        // [nirr] voxel of each irregular voxel
     int32_t *irr_j = nullptr;      // [8][nirr] enriched index per corner or -1
     int32_t *irr_lab = nullptr;    // [6][2][nirr] element labels: uncut (both) or (+ side, - side)
+    int32_t *irr_node = nullptr;   // [8][nirr] node of each corner
+    // elements of the irregular voxels as 6 q + t (voxel q, Kuhn tet t), ascending
+    int32_t *tet_cut = nullptr, *tet_uncut = nullptr;
+    int32_t *cut_pos = nullptr;    // [6 nirr] position in tet_cut, or -1
+    int32_t *blk_cut = nullptr;    // [blocks + 1] first cut element of each run of IRR_VB voxels
+    int32_t *cut_lab = nullptr;    // [2][cut elements] labels of the smaller and the larger side
+    int32_t *uncut_lab = nullptr;  // [uncut elements]
     int32_t *jlist = nullptr;      // [nX]
     int32_t *enr_src = nullptr;    // [nX][8] 8 * irregular voxel + corner feeding enriched node j, or -1
     double *d0 = nullptr;          // [nX]

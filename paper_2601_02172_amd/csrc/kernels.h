@@ -36,6 +36,13 @@ void launch_operator_ws(xfft_problem *p, const Tables<T> &tb, const T *x, const 
                         const double *ebar, bool use_ebar, T sign, int nrhs, const Flags *flags, int parity,
                         double *vstress, hipStream_t s, bool stress, T *cutbuf, double *partial, bool allow_vm);
 
+// Corner forces of the irregular voxels into cutbuf (moment form).
+template <typename T>
+void launch_irregular(xfft_problem *p, const Tables<T> &tb, const T *x, const T *xe, const double *ebar, bool use_ebar,
+                      int nrhs, const Flags *flags, int parity, double *vstress, hipStream_t s, bool stress, T *cutbuf,
+                      double *partial);
+void launch_vm_build(xfft_problem *p, double *K64, float *K32);
+
 // Cached voxel matrices (0; -2 allocation failed; -3 device error) and their release.
 int build_voxel_matrices(xfft_problem *p, bool fp32, bool fp64);
 void free_voxel_matrices(xfft_problem *p);

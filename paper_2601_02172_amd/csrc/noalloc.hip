@@ -91,7 +91,7 @@ extern "C" int xfft_apply_operator_noalloc(xfft_problem *p, const double *x_dev,
                                cutbuf, partial, false);
     const SlotLayout &L = p->slots;
     if (avg_stress_dev)
-        k_avg_stress<<<1, 256, 0, s>>>(partial, L.fe0, L.fe_n, L.cut0, L.cut_n + L.enr_n, (double)g.N,
+        k_avg_stress<<<1, 256, 0, s>>>(partial, L.fe0, L.fe_n, L.enr0, L.enr_n + L.cut_n, (double)g.N,
                                        avg_stress_dev);
     if (hipGetLastError() != hipSuccess) return XFFT_EDEVICE;
     return XFFT_OK;

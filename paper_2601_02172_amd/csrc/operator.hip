@@ -1,10 +1,10 @@
 // Matrix-free scaled X-FEM operator (eqs. linearSystem_element, resVector).
 //
 // Two kernels per application, all deterministic (no atomics):
-//  k_irregular  one thread per irregular voxel (a voxel with a cut element or
-//               elements of different materials); evaluates its six elements
-//               (cut ones by the per-side moment form of element.h) and writes
-//               the eight corner forces (3 FE + 3 scaled enriched) to a buffer;
+//  k_irregular  (irregular.hip) the irregular voxels -- those with a cut
+//               element or elements of different materials -- element by
+//               element; writes their eight corner forces (3 FE + 3 scaled
+//               enriched) to a buffer;
 //  k_regular    z-marching LDS tile over the whole grid: every thread owns a
 //               column of voxels, evaluates the six Kuhn elements of one voxel
 //               per plane (or takes the buffered corner forces of an irregular
@@ -15,7 +15,7 @@
 #include "kernels.h"
 #include <algorithm>
 #include <type_traits>
-#include "element.h"
+#include "op_common.h"
 
 namespace xfft {
 
@@ -25,23 +25,6 @@ constexpr int TE = 16;          // tile edge in threads
 constexpr int TO = TE - 1;      // owned nodes per tile edge
 constexpr int TC = TE + 1;      // node columns per tile edge (halo on the + side)
 
-__device__ __forceinline__ int wrapi(int a, int n) { return a < 0 ? a + n : (a >= n ? a - n : a); }
-
-// Position of value k (0..23: corner k / 3, component k % 3) of irregular voxel q
-// in one half of the corner-force buffer: groups of 64 voxels, six rows of four
-// values per voxel, rows of the 64 voxels adjacent.  The irregular kernel writes
-// a whole row per lane and a wave covers a contiguous block; the regular kernel
-// reads a voxel's 24 values as six 4-vectors.
-__device__ __forceinline__ uint32_t cut_index(uint32_t q, int k) {
-    return (((q >> 6) * 6 + (uint32_t)(k >> 2)) * 64 + (q & 63)) * 4 + (uint32_t)(k & 3);
-}
-
-// base[i] with a 32-bit byte offset (uniform base pointer + 32-bit lane offset)
-template <typename P> __device__ __forceinline__ P &elem(P *base, uint32_t i) {
-    using B = typename std::conditional<std::is_const<P>::value, const char, char>::type;
-    return *reinterpret_cast<P *>(reinterpret_cast<B *>(base) + (uint32_t)(i * (uint32_t)sizeof(P)));
-}
-
 template <typename T>
 struct OpArgs {
     const T *x, *xe;
@@ -50,10 +33,8 @@ struct OpArgs {
     T sign;
     const Flags *flags;
     int parity;
-    const int32_t *vmat, *irr, *irr_j, *irr_lab, *jlist, *enr_src;
-    const T *d0is, *lame;
-    const T *irr_L;           // [8][nirr] corner level set
-    const T *irr_M;           // [6][10][nirr] precomputed moments of the smaller side
+    const int32_t *vmat, *enr_src;
+    const T *lame;
     T *cutbuf;
     double *partial;
     int nslots, slot0;
@@ -61,7 +42,7 @@ struct OpArgs {
     int n0, n1, n2;
     int64_t N, nX, nirr;
     int kz, tiles_x;
-    int tiles_xy, reg_blocks, cut_blocks, enr_blocks;   // workgroups per right-hand side
+    int tiles_xy, reg_blocks, enr_blocks;   // workgroups per right-hand side
     int nrhs;                 // right-hand sides of the launch
     int enr_slot0;            // first partial slot of the enriched gather
 };
@@ -69,27 +50,6 @@ struct OpArgs {
 template <typename T>
 __device__ __forceinline__ bool rhs_active(const OpArgs<T> &A, int r) {
     return A.flags == nullptr || A.flags[r].active[A.parity] != 0;
-}
-
-template <typename T>
-__device__ __forceinline__ Sym<T> load_ebar(const double *e) {
-    T m[6];
-#pragma unroll
-    for (int q = 0; q < 6; ++q) m[q] = (T)e[q];
-    return from_mandel<T>(m);
-}
-
-template <typename T>
-__device__ __forceinline__ void add_sym(double (&acc)[7], const Sym<T> &s) {
-    acc[1] += (double)s.xx; acc[2] += (double)s.yy; acc[3] += (double)s.zz;
-    acc[4] += (double)s.yz; acc[5] += (double)s.xz; acc[6] += (double)s.xy;
-}
-
-template <typename T>
-__device__ __forceinline__ void store_vstress(double *vs, int64_t N, int64_t v, const Sym<T> &s) {
-    const double r2 = 1.41421356237309504880;
-    vs[0 * N + v] = (double)s.xx; vs[1 * N + v] = (double)s.yy; vs[2 * N + v] = (double)s.zz;
-    vs[3 * N + v] = r2 * (double)s.yz; vs[4 * N + v] = r2 * (double)s.xz; vs[5 * N + v] = r2 * (double)s.xy;
 }
 
 // ---------------------------------------------------------------- regular voxel: 6 Kuhn tets
@@ -411,185 +371,6 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
     }
 }
 
-// ---------------------------------------------------------------- irregular voxel
-// M, lab: moment and label tables (rows nirr apart, irregular voxel qv fastest).
-template <int t, typename T, bool EB>
-__device__ __forceinline__ void irregular_tet(const T (&Lc)[8], const T *__restrict__ M, int64_t nirr, uint32_t qv,
-                                              const T (&U)[8][3], const T (&Q)[8][3],
-                                              const int32_t *lab, const T *lame, const Sym<T> &eb,
-                                              T (&F)[8][3], T (&Fe)[8][3], Sym<T> &S) {
-    constexpr int p0 = perm_axis(t, 0), p1 = perm_axis(t, 1), p2 = perm_axis(t, 2);
-    T L[4], u[4][3], q[4][3];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-        L[a] = Lc[tet_corner(t, a)];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) { u[a][i] = U[tet_corner(t, a)][i]; q[a][i] = Q[tet_corner(t, a)][i]; }
-    }
-    const bool anyp = L[0] > (T)0 || L[1] > (T)0 || L[2] > (T)0 || L[3] > (T)0;
-    const bool anyn = L[0] < (T)0 || L[1] < (T)0 || L[2] < (T)0 || L[3] < (T)0;
-    const T V = (T)(1.0 / 6.0);
-    const Grad<T> HF = kuhn_grad<t>(u);
-    if (!(anyp && anyn)) {
-        const int m = elem(lab + (2 * t) * nirr, qv);
-        Sym<T> e = sym_of(HF);
-        if constexpr (EB) {
-            e.xx += eb.xx; e.yy += eb.yy; e.zz += eb.zz; e.yz += eb.yz; e.xz += eb.xz; e.xy += eb.xy;
-        }
-        const Sym<T> s = hooke(e, V * lame[2 * m], V * (T)2 * lame[2 * m + 1]);
-        kuhn_scatter<t>(s, F);
-        sym_axpy(S, (T)1, s);
-        return;
-    }
-    // Side moments: the smaller side was computed in FP64 at setup and rounded
-    // once (as a difference of O(1) moments it would lose all digits in FP32);
-    // the larger side is its complement.
-    T Mp[4][4], Mm[4][4];
-    {
-        T ms[10];
-#pragma unroll
-        for (int e = 0; e < 10; ++e) ms[e] = elem(M + (t * 10 + e) * nirr, qv);
-        const bool pos = !signbit(ms[0]);
-        ms[0] = fabs(ms[0]);
-        T Ms[4][4];
-        int k = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int d = c; d < 4; ++d, ++k) Ms[c][d] = Ms[d][c] = ms[k];
-        complete_sides<T>(Ms, pos, V, Mp, Mm);
-    }
-    const Grad<T> Hq = kuhn_grad<t>(q);
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
-        const T sg = side == 0 ? (T)1 : (T)-1;
-        const int m = elem(lab + (2 * t + side) * nirr, qv);
-        const T lam = lame[2 * m], mu2 = (T)2 * lame[2 * m + 1];
-        T w[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) w[a] = fabs(L[a]) - sg * L[a];
-        // G_s = sum_a w_a g_a with g0 = -e_p0, g1 = e_p0 - e_p1, g2 = e_p1 - e_p2, g3 = e_p2
-        T G[3];
-        G[p0] = w[1] - w[0];
-        G[p1] = w[2] - w[1];
-        G[p2] = w[3] - w[2];
-        Sym<T> Sh[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) Sh[d] = sym_acc_zero<T>();
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            Grad<T> K;
-#pragma unroll
-            for (int pp = 0; pp < 3; ++pp)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) K.h[pp][i] = HF.h[pp][i] + w[c] * Hq.h[pp][i] + q[c][i] * G[pp];
-            Sym<T> e = sym_of(K);
-            if constexpr (EB) {
-                e.xx += eb.xx; e.yy += eb.yy; e.zz += eb.zz; e.yz += eb.yz; e.xz += eb.xz; e.xy += eb.xy;
-            }
-            const Sym<T> sc = hooke(e, lam, mu2);
-            const T *Mrow = side == 0 ? Mp[c] : Mm[c];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) sym_axpy(Sh[d], Mrow[d], sc);
-        }
-        Sym<T> St = sym_acc_zero<T>(), Sw = sym_acc_zero<T>();
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            sym_axpy(St, (T)1, Sh[d]);
-            sym_axpy(Sw, w[d], Sh[d]);
-        }
-        kuhn_scatter<t>(St, F);
-        kuhn_scatter<t>(Sw, Fe);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            const int c = tet_corner(t, a);
-            const Sym<T> &s = Sh[a];
-            Fe[c][0] += s.xx * G[0] + s.xy * G[1] + s.xz * G[2];
-            Fe[c][1] += s.xy * G[0] + s.yy * G[1] + s.yz * G[2];
-            Fe[c][2] += s.xz * G[0] + s.yz * G[1] + s.zz * G[2];
-        }
-        sym_axpy(S, (T)1, St);
-    }
-}
-
-// ST: accumulate the stress integral (criterion 0 and output passes); without
-// it the partial-sum slots carry only the dot product, as in k_regular.
-template <typename T, bool HX, bool EB, bool ST>
-__global__ __launch_bounds__(128) void k_irregular(OpArgs<T> A) {
-    __shared__ double red[2 * 7];
-    const int64_t lb = xcd_remap(blockIdx.x, gridDim.x);
-    const int r = (int)(lb / A.cut_blocks), blk = (int)(lb % A.cut_blocks);
-    if (!rhs_active(A, r)) return;
-    const int64_t qv = (int64_t)blk * blockDim.x + threadIdx.x;
-    const uint32_t q32 = (uint32_t)qv;
-    double acc7[7] = {0, 0, 0, 0, 0, 0, 0};
-    if (qv < A.nirr) {
-        const int64_t N = A.N;
-        const int64_t vox = A.irr[qv];
-        const int i = (int)(vox % A.n0), j = (int)((vox / A.n0) % A.n1), k = (int)(vox / ((int64_t)A.n0 * A.n1));
-        T Lc[8];
-        T U[8][3], Q[8][3], sc[8];
-        const T *x = HX ? A.x + (int64_t)r * 3 * N : nullptr;
-        const T *xe = HX ? A.xe + (int64_t)r * 3 * A.nX : nullptr;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const int64_t node = wrapi(i + (c & 1), A.n0) +
-                                 (int64_t)A.n0 * (wrapi(j + ((c >> 1) & 1), A.n1) + (int64_t)A.n1 * wrapi(k + (c >> 2), A.n2));
-            Lc[c] = elem(A.irr_L + c * A.nirr, q32);
-            const int jc = elem(A.irr_j + c * A.nirr, q32);
-            sc[c] = jc >= 0 ? A.d0is[jc] : (T)0;
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                U[c][d] = HX ? x[d * N + node] : (T)0;
-                Q[c][d] = (HX && jc >= 0) ? sc[c] * xe[d * A.nX + jc] : (T)0;
-            }
-        }
-        Sym<T> eb = sym_zero<T>();
-        if constexpr (EB) eb = load_ebar<T>(A.ebar + 6 * r);
-        const int32_t *lab = A.irr_lab;
-        T F[8][3], Fe[8][3];
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) F[c][d] = Fe[c][d] = acc_zero<T>();
-        Sym<T> S = sym_acc_zero<T>();
-        irregular_tet<0, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        irregular_tet<1, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        irregular_tet<2, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        irregular_tet<3, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        irregular_tet<4, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        irregular_tet<5, T, EB>(Lc, A.irr_M, A.nirr, q32, U, Q, lab, A.lame, eb, F, Fe, S);
-        // per-load buffer: FE corner forces [8][3][nirr], then scaled enriched ones [8][3][nirr]
-        T *cb = A.cutbuf + (int64_t)r * cut_rows(A.nirr) * 48;
-        T *cbe = cb + cut_rows(A.nirr) * 24;
-        T vf[24], ve[24];
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                vf[3 * c + i] = F[c][i];
-                ve[3 * c + i] = sc[c] * Fe[c][i];
-            }
-        using V4 = typename std::conditional<sizeof(T) == 4, float4, double4>::type;
-#pragma unroll
-        for (int k4 = 0; k4 < 6; ++k4) {
-            const uint32_t o = cut_index(q32, 4 * k4) >> 2;
-            elem(reinterpret_cast<V4 *>(cb), o) = V4{vf[4 * k4], vf[4 * k4 + 1], vf[4 * k4 + 2], vf[4 * k4 + 3]};
-            elem(reinterpret_cast<V4 *>(cbe), o) = V4{ve[4 * k4], ve[4 * k4 + 1], ve[4 * k4 + 2], ve[4 * k4 + 3]};
-        }
-        if constexpr (ST) {
-            add_sym(acc7, S);
-            if (A.vstress) store_vstress(A.vstress + (int64_t)r * 6 * N, N, vox, S);
-        }
-    }
-    block_sum<7>(acc7, red);
-    if (threadIdx.x == 0) {
-        double *P = A.partial + ((int64_t)r * A.nslots + A.slot0 + blk) * NPART;
-#pragma unroll
-        for (int q = 0; q < 7; ++q) P[q] = acc7[q];
-    }
-}
-
 // ---------------------------------------------------------------- enriched gather
 // Workgroup blk (256 threads) of load r: one enriched node per thread.
 template <typename T, bool HX>
@@ -633,66 +414,6 @@ __device__ __forceinline__ void enriched_block(const OpArgs<T> &A, int r, int bl
 }
 
 // ---------------------------------------------------------------- cached voxel matrices
-// Column k of the matrix of irregular voxel q: the voxel's forces for the unit
-// input dof k (k < 24: FE component k % 3 of corner k / 3; k >= 24: enriched
-// dof (k - 24) of the corner, entering scaled by D0^-1/2), by the moment form
-// above in FP64; the outputs are the FE corner forces and the scaled enriched
-// corner forces, as the irregular-voxel kernel writes them.  Column k supplies
-// the rows i <= k of the packed upper triangle and the stress integral.
-__global__ __launch_bounds__(128) void k_vm_build(OpArgs<double> A, double *K64, float *K32) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t q = t / 48;
-    const int k = (int)(t - q * 48);
-    if (q >= A.nirr) return;
-    const uint32_t q32 = (uint32_t)q;
-    double Lc[8], U[8][3], Q[8][3], sc[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        Lc[c] = elem(A.irr_L + c * A.nirr, q32);
-        const int jc = elem(A.irr_j + c * A.nirr, q32);
-        sc[c] = jc >= 0 ? A.d0is[jc] : 0.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            U[c][d] = (k < 24 && 3 * c + d == k) ? 1.0 : 0.0;
-            Q[c][d] = (k >= 24 && 3 * c + d == k - 24) ? sc[c] : 0.0;
-        }
-    }
-    const Sym<double> eb = sym_zero<double>();
-    double F[8][3], Fe[8][3];
-#pragma unroll
-    for (int c = 0; c < 8; ++c)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) F[c][d] = Fe[c][d] = acc_zero<double>();
-    Sym<double> S = sym_acc_zero<double>();
-    irregular_tet<0, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    irregular_tet<1, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    irregular_tet<2, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    irregular_tet<3, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    irregular_tet<4, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    irregular_tet<5, double, false>(Lc, A.irr_M, A.nirr, q32, U, Q, A.irr_lab, A.lame, eb, F, Fe, S);
-    double *k64 = K64 + q * VM_STRIDE;
-    float *k32 = K32 ? K32 + q * VM_STRIDE : nullptr;
-#pragma unroll
-    for (int i = 0; i < 48; ++i) {
-        if (i <= k) {
-            const int c = (i < 24 ? i : i - 24) / 3, d = (i < 24 ? i : i - 24) % 3;
-            const double v = i < 24 ? F[c][d] : sc[c] * Fe[c][d];
-            k64[vm_row(i) + k] = v;
-            if (k32) k32[vm_row(i) + k] = (float)v;
-        }
-    }
-    const double st[6] = {S.xx, S.yy, S.zz, S.yz, S.xz, S.xy};
-#pragma unroll
-    for (int m = 0; m < 6; ++m) {
-        k64[VM_KP + 48 * m + k] = st[m];
-        if (k32) k32[VM_KP + 48 * m + k] = (float)st[m];
-    }
-    if (k < VM_KP - VM_K) {
-        k64[VM_K + k] = 0.0;
-        if (k32) k32[VM_K + k] = 0.0f;
-    }
-}
-
 template <typename T> struct VmArgs {
     const T *x, *xe;          // inputs of load 0; loads 3 N / 3 nX apart
     T *cutbuf;                // corner-force buffer of load 0
@@ -901,14 +622,14 @@ void launch_operator_ws(xfft_problem *p, const Tables<T> &tb, const T *x, const 
     OpArgs<T> A;
     A.x = x; A.xe = xe; A.y = y; A.ye = ye;
     A.ebar = ebar; A.sign = sign; A.flags = flags; A.parity = parity;
-    A.vmat = p->vmat; A.irr = p->irr; A.irr_j = p->irr_j; A.irr_lab = p->irr_lab; A.jlist = p->jlist;
+    A.vmat = p->vmat;
     A.enr_src = p->enr_src;
-    A.irr_L = tb.irr_L; A.irr_M = tb.irr_M; A.d0is = tb.d0is; A.lame = tb.lame;
+    A.lame = tb.lame;
     A.cutbuf = cutbuf; A.partial = partial; A.nslots = p->nslots;
     A.vstress = vstress;
     A.n0 = g.n0; A.n1 = g.n1; A.n2 = g.n2; A.N = g.N; A.nX = g.nX; A.nirr = g.nirr;
     A.kz = L.kz; A.tiles_x = L.tiles_x;
-    A.tiles_xy = L.tiles_x * L.tiles_y; A.reg_blocks = L.tiles_x * L.tiles_y * L.zchunks; A.cut_blocks = L.cut_n;
+    A.tiles_xy = L.tiles_x * L.tiles_y; A.reg_blocks = L.tiles_x * L.tiles_y * L.zchunks;
     A.enr_blocks = L.enr_n;
     A.nrhs = nrhs;
     A.enr_slot0 = L.enr0;
@@ -932,15 +653,7 @@ void launch_operator_ws(xfft_problem *p, const Tables<T> &tb, const T *x, const 
         else launch_vm<T, 6>(V, grid, stress, s);
         xfft_prof_mark(p, K_IRREGULAR + (sizeof(T) == 8 ? K_COUNT : 0), s);
     } else if (g.nirr > 0) {
-        A.slot0 = L.cut0;
-        dim3 grid((unsigned)L.cut_n * nrhs, 1);
-        xfft_prof_mark(p, -1, s);
-        if (hx && use_ebar) k_irregular<T, true, true, true><<<grid, 128, 0, s>>>(A);
-        else if (hx && stress) k_irregular<T, true, false, true><<<grid, 128, 0, s>>>(A);
-        else if (hx) k_irregular<T, true, false, false><<<grid, 128, 0, s>>>(A);
-        else if (use_ebar) k_irregular<T, false, true, true><<<grid, 128, 0, s>>>(A);
-        else k_irregular<T, false, false, false><<<grid, 128, 0, s>>>(A);
-        xfft_prof_mark(p, K_IRREGULAR + (sizeof(T) == 8 ? K_COUNT : 0), s);
+        launch_irregular<T>(p, tb, x, xe, ebar, use_ebar, nrhs, flags, parity, vstress, s, stress, cutbuf, partial);
     }
     {
         A.slot0 = L.fe0;
@@ -980,11 +693,7 @@ int build_voxel_matrices(xfft_problem *p, bool fp32, bool fp64) {
         if (hipMalloc(&k64, n * sizeof(double)) != hipSuccess) return -2;
         tmp = true;
     }
-    OpArgs<double> A{};
-    A.irr_j = p->irr_j; A.irr_lab = p->irr_lab; A.irr_L = p->t64.irr_L; A.irr_M = p->t64.irr_M;
-    A.d0is = p->t64.d0is; A.lame = p->t64.lame; A.nirr = g.nirr;
-    const int64_t nt = g.nirr * 48;
-    k_vm_build<<<(unsigned)((nt + 127) / 128), 128, 0, p->stream>>>(A, k64, p->vm32);
+    launch_vm_build(p, k64, p->vm32);
     const bool ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(p->stream) == hipSuccess;
     if (tmp) (void)hipFree(k64);
     if (!ok) return -3;
@@ -1032,9 +741,13 @@ SlotLayout slot_layout(const Geometry &g) {
     L.fe_cap = L.tiles_x * L.tiles_y * ((g.n2 + 3) / 4);
     at += L.fe_cap;
     set_depth(L, g, kz);
-    L.cut0 = at; L.cut_n = (int)((g.nirr + 127) / 128); at += L.cut_n;
     L.enr0 = at; L.enr_n = (int)((g.nX + 255) / 256); at += L.enr_n;
-    L.vm0 = at; L.vm_n = (int)std::min<int64_t>((g.nirr + VM_VPB - 1) / VM_VPB, VM_GRID); at += L.vm_n;
+    // one operator application runs either the moment form or the cached
+    // matrices: their slots share one range, right after the enriched ones
+    L.cut0 = L.vm0 = at;
+    L.cut_n = (int)((g.nirr + IRR_VB - 1) / IRR_VB);
+    L.vm_n = (int)std::min<int64_t>((g.nirr + VM_VPB - 1) / VM_VPB, VM_GRID);
+    at += std::max(L.cut_n, L.vm_n);
     L.grn0 = at; L.grn_n = 0; // filled by the FFT planner
     L.total = at;
     return L;

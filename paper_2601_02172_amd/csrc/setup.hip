@@ -157,9 +157,11 @@ __global__ __launch_bounds__(1024) void k_scan_offsets(int nb, const int32_t *cn
 }
 
 // Emit in order: for voxels, irr[pos] = v and vmat[v] = -(pos + 1) (or the label);
-// for nodes, jlist[pos] = node and jmap[node] = pos (or -1).
+// for nodes, jlist[pos] = node and jmap[node] = pos (or -1).  comp, if given,
+// takes the others in order.
 __global__ __launch_bounds__(SCAN_T) void k_scan_emit(int64_t n, const uint8_t *flag, const int32_t *off,
-                                                       int32_t *list, int32_t *map, const int32_t *lab) {
+                                                       int32_t *list, int32_t *map, const int32_t *lab,
+                                                       int32_t *comp) {
     __shared__ int32_t pre[SCAN_T];
     const int64_t base = (int64_t)blockIdx.x * SCAN_CH + (int64_t)threadIdx.x * SCAN_PER;
     int c = 0;
@@ -185,6 +187,7 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_emit(int64_t n, const uint8_t *
             ++pos;
         } else {
             map[i] = lab ? lab[i] : -1;
+            if (comp) comp[i - pos] = (int32_t)i;
         }
     }
 }
@@ -226,68 +229,100 @@ __global__ void k_irr_tables(int64_t nirr, int n0, int n1, int n2, const int32_t
     irr_labels_tet<5>(Lc, pc, lab, nirr);
 }
 
-// Side moments of the six Kuhn tets of every irregular voxel (exact
-// integration over the two sides of a cut element): geometry only, so they are
-// computed once per setup in FP64 instead of in every operator application.
-// Stored per tet, 10 values [t][e][qv] (irregular voxel fastest, so that the
-// lanes of a wave read consecutive words): the upper triangle (row by row) of
-// the moments of the side with the smaller volume, whose entry 0 carries the
-// sign bit when that side is the - side (all moments are >= 0).  The operator
-// forms the other side as the complement M^tet - Ms, which is accurate in FP32
-// because it is the larger side.
-__global__ void k_irr_moments(int64_t nirr, const double *irr_L64, double *M64, float *M32) {
+// node of every corner and, per element 6 q + t, whether it is cut
+__global__ void k_tet_flags(int64_t nirr, int n0, int n1, int n2, const int32_t *irr, const double *irr_L64,
+                            int32_t *irr_node, uint8_t *cut) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nirr) return;
+    const int64_t v = irr[q];
+    const int i = (int)(v % n0), j = (int)((v / n0) % n1), k = (int)(v / ((int64_t)n0 * n1));
     double Lc[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) Lc[c] = irr_L64[c * nirr + q];
+    for (int c = 0; c < 8; ++c) {
+        Lc[c] = irr_L64[c * nirr + q];
+        irr_node[c * nirr + q] = (int32_t)corner_node(i, j, k, c, n0, n1, n2);
+    }
+#pragma unroll
     for (int t = 0; t < 6; ++t) {
-        double L[4];
         bool anyp = false, anyn = false;
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            L[a] = Lc[tet_corner(t, a)];
-            anyp |= L[a] > 0.0;
-            anyn |= L[a] < 0.0;
+            anyp |= Lc[tet_corner(t, a)] > 0.0;
+            anyn |= Lc[tet_corner(t, a)] < 0.0;
         }
-        double Ms[4][4];
-        bool pos = true;
-        if (anyp && anyn) {
-            pos = small_side_moments<double>(L, 1.0 / 6.0, Ms);
-            // keep the side of smaller volume (sum of the moments): its
-            // complement is then the larger side and is formed accurately in FP32
-            const double Vt = (1.0 / 6.0) * 0.05;
-            double vs = 0.0;
+        cut[6 * q + t] = anyp && anyn ? 1 : 0;
+    }
+}
+
+// first cut element of every run of IRR_VB irregular voxels (lower bound of 6 q0 in the ascending list)
+__global__ void k_blk_cut(int nblk, int64_t ncut, const int32_t *tet_cut, int32_t *blk_cut) {
+    const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    if (b > nblk) return;
+    const int64_t key = (int64_t)6 * IRR_VB * b;
+    int64_t lo = 0, hi = ncut;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) / 2;
+        if (tet_cut[mid] < key) lo = mid + 1;
+        else hi = mid;
+    }
+    blk_cut[b] = (int32_t)lo;
+}
+
+__global__ void k_uncut_lab(int64_t n, int64_t nirr, const int32_t *tet_uncut, const int32_t *irr_lab, int32_t *lab) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int q = tet_uncut[i] / 6, t = tet_uncut[i] - 6 * q;
+    lab[i] = irr_lab[(int64_t)(2 * t) * nirr + q];
+}
+
+// Side moments of every cut element (exact integration over its two sides):
+// geometry only, so they are computed once per setup in FP64 instead of in every
+// operator application.  Stored as 10 values [e][i] (element fastest, so that
+// the lanes of a wave read consecutive words): the upper triangle (row by row)
+// of the moments of the side with the smaller volume, whose entry 0 carries the
+// sign bit when that side is the - side (all moments are >= 0), and the labels
+// of the smaller and the larger side.  The operator forms the other side as the
+// complement M^tet - Ms, which is accurate in FP32 because it is the larger side.
+__global__ void k_cut_moments(int64_t ncut, int64_t nirr, const int32_t *tet_cut, const double *irr_L64,
+                              const int32_t *irr_lab, double *M64, float *M32, int32_t *cut_lab) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= ncut) return;
+    const int q = tet_cut[i] / 6, t = tet_cut[i] - 6 * q;
+    double L[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
+    for (int a = 0; a < 4; ++a) L[a] = irr_L64[tet_corner(t, a) * nirr + q];
+    double Ms[4][4];
+    bool pos = small_side_moments<double>(L, 1.0 / 6.0, Ms);
+    // keep the side of smaller volume (sum of the moments): its complement is
+    // then the larger side and is formed accurately in FP32
+    const double Vt = (1.0 / 6.0) * 0.05;
+    double vs = 0.0;
 #pragma unroll
-                for (int d = 0; d < 4; ++d) vs += Ms[c][d];
-            if (vs > 0.5 * (20.0 * Vt)) {      // the whole tet: sum of V (1 + delta_cd) / 20 = V
+    for (int c = 0; c < 4; ++c)
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) Ms[c][d] = Vt * (c == d ? 2.0 : 1.0) - Ms[c][d];
-                pos = !pos;
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-#pragma unroll
-                for (int d = 0; d < 4; ++d) Ms[c][d] = 0.0;
-        }
-        double v[10];
-        int k = 0;
+        for (int d = 0; d < 4; ++d) vs += Ms[c][d];
+    if (vs > 0.5 * (20.0 * Vt)) {      // the whole tet: sum of V (1 + delta_cd) / 20 = V
 #pragma unroll
         for (int c = 0; c < 4; ++c)
 #pragma unroll
-            for (int d = c; d < 4; ++d, ++k) v[k] = Ms[c][d];
-        if (!pos) v[0] = -v[0];                       // sign bit marks the - side (also for +0)
-#pragma unroll
-        for (int e = 0; e < 10; ++e) {
-            M64[(t * 10 + e) * nirr + q] = v[e];
-            M32[(t * 10 + e) * nirr + q] = (float)v[e];
-        }
+            for (int d = 0; d < 4; ++d) Ms[c][d] = Vt * (c == d ? 2.0 : 1.0) - Ms[c][d];
+        pos = !pos;
     }
+    double v[10];
+    int k = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int d = c; d < 4; ++d, ++k) v[k] = Ms[c][d];
+    if (!pos) v[0] = -v[0];                       // sign bit marks the - side (also for +0)
+#pragma unroll
+    for (int e = 0; e < 10; ++e) {
+        M64[e * ncut + i] = v[e];
+        M32[e * ncut + i] = (float)v[e];
+    }
+    const int lp = irr_lab[(int64_t)(2 * t) * nirr + q], ln = irr_lab[(int64_t)(2 * t + 1) * nirr + q];
+    cut_lab[i] = pos ? lp : ln;
+    cut_lab[ncut + i] = pos ? ln : lp;
 }
 
 // int over both sides of |grad N_X^a|^2 for vertex a of cut Kuhn tet t
@@ -421,7 +456,7 @@ constexpr int XFFT_ENOMEM_INTERNAL = -2;
 constexpr int XFFT_EINVAL_INTERNAL = -1;
 
 int compact(hipStream_t s, int64_t n, const uint8_t *flag, int32_t *map, const int32_t *lab, int32_t **list_out,
-            int64_t *count_out) {
+            int64_t *count_out, int32_t **comp_out = nullptr) {
     const int nb = (int)((n + SCAN_CH - 1) / SCAN_CH);
     int32_t *cnt = nullptr, *off = nullptr;
     int64_t *tot = nullptr;
@@ -437,18 +472,60 @@ int compact(hipStream_t s, int64_t n, const uint8_t *flag, int32_t *map, const i
         rc = XFFT_EDEVICE_INTERNAL;
     int32_t *list = nullptr;
     if (!rc && hipMalloc(&list, sizeof(int32_t) * (total > 0 ? total : 1)) != hipSuccess) rc = XFFT_ENOMEM_INTERNAL;
-    if (!rc) k_scan_emit<<<nb, SCAN_T, 0, s>>>(n, flag, off, list, map, lab);
+    int32_t *comp = nullptr;
+    if (!rc && comp_out && hipMalloc(&comp, sizeof(int32_t) * (n > total ? n - total : 1)) != hipSuccess)
+        rc = XFFT_ENOMEM_INTERNAL;
+    if (!rc) k_scan_emit<<<nb, SCAN_T, 0, s>>>(n, flag, off, list, map, lab, comp);
     if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = XFFT_EDEVICE_INTERNAL;
     (void)hipFree(cnt);
     (void)hipFree(off);
     (void)hipFree(tot);
-    if (rc) { if (list) (void)hipFree(list); return rc; }
+    if (rc) { if (list) (void)hipFree(list); if (comp) (void)hipFree(comp); return rc; }
     *list_out = list;
+    if (comp_out) *comp_out = comp;
     *count_out = total;
     return 0;
 }
 
 }  // namespace
+
+// Lists of the cut and uncut elements of the irregular voxels and their tables.
+static int element_lists(xfft_problem *p) {
+    hipStream_t s = p->stream;
+    const Geometry &g = p->g;
+    const int64_t ne = 6 * g.nirr;
+    uint8_t *cut = nullptr;
+    int64_t nc = 0;
+    int rc = 0;
+    if (hipMalloc(&cut, ne) != hipSuccess || hipMalloc(&p->cut_pos, sizeof(int32_t) * ne) != hipSuccess)
+        rc = XFFT_ENOMEM_INTERNAL;
+    if (!rc) {
+        k_tet_flags<<<(unsigned)((g.nirr + 255) / 256), 256, 0, s>>>(g.nirr, g.n0, g.n1, g.n2, p->irr, p->t64.irr_L,
+                                                                     p->irr_node, cut);
+        rc = compact(s, ne, cut, p->cut_pos, nullptr, &p->tet_cut, &nc, &p->tet_uncut);
+    }
+    const int64_t nu = ne - nc;
+    const int nblk = (int)((g.nirr + IRR_VB - 1) / IRR_VB);
+    const size_t mc = nc > 0 ? nc : 1, mu = nu > 0 ? nu : 1;
+    if (!rc && (nc != p->n_cut_elements || hipMalloc(&p->blk_cut, sizeof(int32_t) * (nblk + 1)) != hipSuccess ||
+                hipMalloc(&p->t64.cut_M, sizeof(double) * 10 * mc) != hipSuccess ||
+                hipMalloc(&p->t32.cut_M, sizeof(float) * 10 * mc) != hipSuccess ||
+                hipMalloc(&p->cut_lab, sizeof(int32_t) * 2 * mc) != hipSuccess ||
+                hipMalloc(&p->uncut_lab, sizeof(int32_t) * mu) != hipSuccess))
+        rc = nc != p->n_cut_elements ? XFFT_EDEVICE_INTERNAL : XFFT_ENOMEM_INTERNAL;
+    if (!rc) {
+        k_blk_cut<<<(unsigned)((nblk + 256) / 256), 256, 0, s>>>(nblk, nc, p->tet_cut, p->blk_cut);
+        if (nc)
+            k_cut_moments<<<(unsigned)((nc + 255) / 256), 256, 0, s>>>(nc, g.nirr, p->tet_cut, p->t64.irr_L,
+                                                                       p->irr_lab, p->t64.cut_M, p->t32.cut_M,
+                                                                       p->cut_lab);
+        if (nu)
+            k_uncut_lab<<<(unsigned)((nu + 255) / 256), 256, 0, s>>>(nu, g.nirr, p->tet_uncut, p->irr_lab,
+                                                                     p->uncut_lab);
+    }
+    if (cut) (void)hipFree(cut);
+    return rc;
+}
 
 // L_dev_raw: device copy of the caller's level set (units of len).
 int run_setup(xfft_problem *p, const double *L_dev_raw) {
@@ -508,8 +585,7 @@ int run_setup(xfft_problem *p, const double *L_dev_raw) {
             hipMalloc(&p->irr_lab, sizeof(int32_t) * 12 * nirr) != hipSuccess ||
             hipMalloc(&p->t64.irr_L, sizeof(double) * 8 * nirr) != hipSuccess ||
             hipMalloc(&p->t32.irr_L, sizeof(float) * 8 * nirr) != hipSuccess ||
-            hipMalloc(&p->t64.irr_M, sizeof(double) * 60 * nirr) != hipSuccess ||
-            hipMalloc(&p->t32.irr_M, sizeof(float) * 60 * nirr) != hipSuccess ||
+            hipMalloc(&p->irr_node, sizeof(int32_t) * 8 * nirr) != hipSuccess ||
             hipMalloc(&p->d0, sizeof(double) * nX) != hipSuccess ||
             hipMalloc(&p->t64.d0is, sizeof(double) * nX) != hipSuccess ||
             hipMalloc(&p->t32.d0is, sizeof(float) * nX) != hipSuccess ||
@@ -520,8 +596,7 @@ int run_setup(xfft_problem *p, const double *L_dev_raw) {
         k_irr_tables<<<(unsigned)((g.nirr + tb - 1) / tb), tb, 0, s>>>(g.nirr, g.n0, g.n1, g.n2, p->irr, p->Ls,
                                                                        p->phase, jmap, p->irr_j, p->irr_lab,
                                                                        p->t64.irr_L, p->t32.irr_L);
-        k_irr_moments<<<(unsigned)((g.nirr + tb - 1) / tb), tb, 0, s>>>(g.nirr, p->t64.irr_L, p->t64.irr_M,
-                                                                        p->t32.irr_M);
+        rc = element_lists(p);
     }
     if (!rc && g.nX > 0) {
         k_d0<<<(unsigned)((g.nX + tb - 1) / tb), tb, 0, s>>>(g.nX, g.n0, g.n1, g.n2, p->jlist, p->vmat, p->t64.irr_L,
