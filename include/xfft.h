@@ -122,8 +122,8 @@ typedef struct {
                                solve of a precision, the fastest kept (with autotune on; else 0); or fixed: bit 0
                                set = separate x and y passes instead of the xy-plane kernels (grids with
                                n0 = n1 in {16, 32, 48, 64, 96, 128}), bit 1 set = the alternative z-pass tile
-                               (twice the kx columns per workgroup at n2 = 256, half of them for the other
-                               compile-time lengths 16 ... 128).  A bit a grid has no choice for is ignored.
+                               (twice the kx columns per workgroup for n2 above 144, half of them for the
+                               other compile-time lengths 12 ... 256).  A bit a grid has no choice for is ignored.
                                Every variant computes the same transform. */
 } xfft_options;
 

@@ -844,6 +844,8 @@ void xfft_destroy(xfft_problem *p) {
         if (p->t64.half[a]) (void)hipFree(p->t64.half[a]);
         if (p->t32.half[a]) (void)hipFree(p->t32.half[a]);
     }
+    if (p->t64.twp) (void)hipFree(p->t64.twp);
+    if (p->t32.twp) (void)hipFree(p->t32.twp);
     drop_graph(p);
     free_voxel_matrices(p);
     free_work(p->w64);

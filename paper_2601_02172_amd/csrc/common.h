@@ -122,6 +122,7 @@ template <typename T> struct Tables {
     T *cut_M = nullptr;
     cpx<T> *tw[3] = {nullptr, nullptr, nullptr};   // twiddles exp(-2 pi i t / n_axis)
     cpx<T> *tws[3] = {nullptr, nullptr, nullptr};  // stage-major twiddles of the compile-time LDS FFT
+    cpx<T> *twp = nullptr;                         // the same for the plan of the xy-plane kernels (x axis)
     T *half[3] = {nullptr, nullptr, nullptr};      // [n_axis][2]: sin, cos of pi k / n_axis
 };
 

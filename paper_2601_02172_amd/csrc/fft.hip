@@ -378,16 +378,22 @@ __global__ __launch_bounds__(256) void k_fft_x_inv(FftArgs A, FftPlan pl, const 
 // Used when the xy plane does not fit in LDS (e.g. 256^2): the x transform on
 // PP row pairs per workgroup, the y transform on runs of kx columns; both with
 // the LDS Stockham transform of fft_lines.h.  Spectrum layout [c][kz][ky][kx].
-template <int N> struct XCfg {
+// Row pairs per workgroup: about 32 KB of LDS; half of it from 256 on (8 pairs in
+// FP32), which keeps twice the workgroups per CU.  Lengths with a factor 3 take
+// the interleaved layout where a workgroup holds at least 32 lines: its LDS
+// offsets are compile-time constants for every length.
+template <typename T, int N> struct XCfg {
     static constexpr int NH = N / 2 + 1;
-    static constexpr int PP = (N >= 256 ? 2048 : 4096) / N;   // row pairs per workgroup
-    static constexpr int LS = fft_ls(N);
+    static constexpr int PP = (N >= 256 ? 2048 : sizeof(T) == 8 && (N & (N - 1)) ? 2048 : 4096) / N;
+    static constexpr bool ILV = PP >= 32 && (N & (N - 1)) != 0;
+    static constexpr int LS = lds_ls<ILV>(N);
+    static __device__ __forceinline__ int pos(int e) { return lds_pos<ILV>(e); }
 };
 
 template <typename T, int N>
 __global__ __launch_bounds__(256) void k_fft_x_fwd_t(FftArgs A, const cpx<T> *tw, T *f, const T *z, cpx<T> *spec,
                                                       int nrhs) {
-    using C = XCfg<N>;
+    using C = XCfg<T, N>;
     extern __shared__ unsigned char smem_raw[];
     cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
     const int64_t npairs = (int64_t)3 * A.n2 * A.n1 / 2;
@@ -415,16 +421,16 @@ __global__ __launch_bounds__(256) void k_fft_x_fwd_t(FftArgs A, const cpx<T> *tw
                 fr[o1] = b;
             }
         }
-        sh[lp * C::LS + fft_pad(x)] = {a, b};
+        sh[lp * C::LS + C::pos(x)] = {a, b};
     }
     __syncthreads();
-    fft_lines<T, N, C::PP, 256, false>(sh, tw);
+    fft_lines<T, N, C::PP, 256, false, C::ILV>(sh, tw);
     for (int idx = threadIdx.x; idx < C::PP * C::NH; idx += 256) {
         const int lp = idx / C::NH, kx = idx - lp * C::NH;
         const int64_t pr = p0 + lp;
         if (pr < npairs) {
-            const cpx<T> Zk = sh[lp * C::LS + fft_pad(kx)];
-            const cpx<T> Zm = sh[lp * C::LS + fft_pad(kx == 0 ? 0 : N - kx)];
+            const cpx<T> Zk = sh[lp * C::LS + C::pos(kx)];
+            const cpx<T> Zm = sh[lp * C::LS + C::pos(kx == 0 ? 0 : N - kx)];
             sr[(2 * pr) * A.nhs + kx] = {(T)0.5 * (Zk.x + Zm.x), (T)0.5 * (Zk.y - Zm.y)};
             sr[(2 * pr + 1) * A.nhs + kx] = {(T)0.5 * (Zk.y + Zm.y), (T)-0.5 * (Zk.x - Zm.x)};
         }
@@ -443,7 +449,7 @@ __global__ __launch_bounds__(256) void k_fft_x_fwd_t(FftArgs A, const cpx<T> *tw
 template <typename T, int N>
 __global__ __launch_bounds__(256) void k_fft_x_inv_t(FftArgs A, const cpx<T> *tw, const cpx<T> *spec, int mode,
                                                       T *out, T *u, T *d, int nrhs) {
-    using C = XCfg<N>;
+    using C = XCfg<T, N>;
     extern __shared__ unsigned char smem_raw[];
     cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
     const int64_t npairs = (int64_t)3 * A.n2 * A.n1 / 2;
@@ -464,10 +470,10 @@ __global__ __launch_bounds__(256) void k_fft_x_inv_t(FftArgs A, const cpx<T> *tw
             if (!lo) { Av.y = -Av.y; Bv.y = -Bv.y; }
             Zv = {Av.x - Bv.y, Av.y + Bv.x};
         }
-        sh[lp * C::LS + fft_pad(k)] = Zv;
+        sh[lp * C::LS + C::pos(k)] = Zv;
     }
     __syncthreads();
-    fft_lines<T, N, C::PP, 256, true>(sh, tw);
+    fft_lines<T, N, C::PP, 256, true, C::ILV>(sh, tw);
     const int64_t rN = (int64_t)r * 3 * A.N;
     T alpha = 0, beta = 0;
     if (mode == 1) { alpha = (T)A.scal[r].alpha; beta = (T)A.scal[r].beta; }
@@ -475,7 +481,7 @@ __global__ __launch_bounds__(256) void k_fft_x_inv_t(FftArgs A, const cpx<T> *tw
         const int lp = idx / N, x = idx - lp * N;
         const int64_t pr = p0 + lp;
         if (pr < npairs) {
-            const cpx<T> yv = sh[lp * C::LS + fft_pad(x)];
+            const cpx<T> yv = sh[lp * C::LS + C::pos(x)];
             const int64_t o0 = rN + (2 * pr) * N + x, o1 = o0 + N;
             if (mode == 0) {
                 out[o0] = yv.x;
@@ -498,7 +504,8 @@ __global__ __launch_bounds__(256) void k_fft_x_inv_t(FftArgs A, const cpx<T> *tw
 // ceil(nh / TK) runs share the nh columns evenly
 template <typename T, int N1, int TK, bool INV>
 __global__ __launch_bounds__(256) void k_fft_y_t(FftArgs A, const cpx<T> *tw, cpx<T> *spec, int nrhs) {
-    constexpr int LS = fft_ls(N1);
+    constexpr bool ILV = TK >= 32 && (N1 & (N1 - 1)) != 0;
+    constexpr int LS = lds_ls<ILV>(N1);
     extern __shared__ unsigned char smem_raw[];
     cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
     const int nh = A.nh;
@@ -513,13 +520,13 @@ __global__ __launch_bounds__(256) void k_fft_y_t(FftArgs A, const cpx<T> *tw, cp
     cpx<T> *base = spec + (int64_t)r * 3 * A.specN + (int64_t)plane * N1 * A.nhs + kx0;
     for (int idx = threadIdx.x; idx < TK * N1; idx += 256) {
         const int kl = idx % TK, yy = idx / TK;
-        if (kl < tk) sh[kl * LS + fft_pad(yy)] = kl < ncol ? base[(int64_t)yy * A.nhs + kl] : cpx<T>{0, 0};
+        if (kl < tk) sh[kl * LS + lds_pos<ILV>(yy)] = kl < ncol ? base[(int64_t)yy * A.nhs + kl] : cpx<T>{0, 0};
     }
     __syncthreads();
-    fft_lines<T, N1, TK, 256, INV>(sh, tw, tk);
+    fft_lines<T, N1, TK, 256, INV, ILV>(sh, tw, tk);
     for (int idx = threadIdx.x; idx < TK * N1; idx += 256) {
         const int kl = idx % TK, yy = idx / TK;
-        if (kl < ncol) base[(int64_t)yy * A.nhs + kl] = sh[kl * LS + fft_pad(yy)];
+        if (kl < ncol) base[(int64_t)yy * A.nhs + kl] = sh[kl * LS + lds_pos<ILV>(yy)];
     }
 }
 
@@ -559,7 +566,7 @@ template <typename T, int N>
 __device__ __forceinline__ void plane_forward_core(cpx<T> *sh, const cpx<T> *tw, const FftArgs &A, cpx<T> *sr,
                                                    int kz, int tid) {
     using C = PlaneCfg<N>;
-    fft_lines<T, N, C::NP, C::NT, false, true>(sh, tw, C::NP, tid);
+    fft_lines<T, N, C::NP, C::NT, false, true, sizeof(T) == 8>(sh, tw, C::NP, tid);
     if constexpr (C::FP) {
         const int kxl = tid % C::KW, ppl = tid / C::KW;
         const int rd = ppl * C::LS + kxl, rdm = ppl * C::LS + (kxl == 0 ? 0 : N - kxl);
@@ -588,7 +595,7 @@ __device__ __forceinline__ void plane_forward_core(cpx<T> *sh, const cpx<T> *tw,
             sh[C::KW * C::LS + 2 * tid + 1] = rb[C::XW];
         }
         __syncthreads();
-        fft_lines<T, N, C::NH, C::NT, false, true>(sh, tw, C::NH, tid);
+        fft_lines<T, N, C::NH, C::NT, false, true, sizeof(T) == 8>(sh, tw, C::NH, tid);
         // spectrum rows ky = kyl + RS m of columns kxl, and the Nyquist column
         const int kyl = ppl;
         cpx<T> *so = sr + ((int64_t)kyl * A.n2 + kz) * C::NH + kxl;
@@ -624,7 +631,7 @@ __device__ __forceinline__ void plane_forward_core(cpx<T> *sh, const cpx<T> *tw,
         }
     }
     __syncthreads();
-    fft_lines<T, N, C::NH, C::NT, false, true>(sh, tw, C::NH, tid);
+    fft_lines<T, N, C::NH, C::NT, false, true, sizeof(T) == 8>(sh, tw, C::NH, tid);
     for (int idx = tid; idx < N * C::NH; idx += C::NT) {
         const int ky = idx / C::NH, kx = idx - ky * C::NH;
         sr[((int64_t)ky * A.n2 + kz) * C::NH + kx] = sh[kx * C::LS + ky];
@@ -675,7 +682,7 @@ __global__ __launch_bounds__(1024) void k_fft_plane_fwd(FftArgs A, const cpx<T> 
 template <typename T, int N>
 __device__ __forceinline__ void plane_inverse_core(cpx<T> *sh, const cpx<T> *tw, int tid) {
     using C = PlaneCfg<N>;
-    fft_lines<T, N, C::NH, C::NT, true, true>(sh, tw, C::NH, tid);
+    fft_lines<T, N, C::NH, C::NT, true, true, sizeof(T) == 8>(sh, tw, C::NH, tid);
     if constexpr (C::FP) {
         // output (row pair ppl + RP i, x = k) for thread (k, ppl) = (tid % N, tid / N)
         constexpr int RP = C::NT / N, NI = C::NP / RP;
@@ -696,7 +703,7 @@ __device__ __forceinline__ void plane_inverse_core(cpx<T> *sh, const cpx<T> *tw,
 #pragma unroll
         for (int i = 0; i < NI; ++i) sh[w0 + i * RP * C::LS] = rz[i];
         __syncthreads();
-        fft_lines<T, N, C::NP, C::NT, true, true>(sh, tw, C::NP, tid);
+        fft_lines<T, N, C::NP, C::NT, true, true, sizeof(T) == 8>(sh, tw, C::NP, tid);
         return;
     }
     constexpr int NOUT = C::NP * N;
@@ -724,7 +731,7 @@ __device__ __forceinline__ void plane_inverse_core(cpx<T> *sh, const cpx<T> *tw,
         }
     }
     __syncthreads();
-    fft_lines<T, N, C::NP, C::NT, true, true>(sh, tw, C::NP, tid);
+    fft_lines<T, N, C::NP, C::NT, true, true, sizeof(T) == 8>(sh, tw, C::NP, tid);
 }
 
 // mode 0: out = G f; mode 1: u += alpha d, d = G f + beta d; mode 2: d = G f
@@ -985,7 +992,22 @@ FftArgs fft_args(xfft_problem *p, const Flags *flags, int parity) {
 static int tk_z(const Geometry &g) { return tk_for<double>(g.n2, 3, 512); }
 
 static bool plane_size(int n) { return n == 16 || n == 32 || n == 48 || n == 64 || n == 96 || n == 128; }
-static bool ztmpl_size(int n) { return plane_size(n) || n == 256; }
+// Lengths with compile-time x, y and z passes: every 2^a 3^b from 12 to 256
+// except 27, 81 and 243 (the axes are even).  Longer and shorter ones take the
+// passes with a plan read at run time, whose radices 4, 2, 3 cost an LDS round
+// trip each (108 = 4 x 3 x 3 x 3 against 9 x 12) and whose indices are divided at
+// run time.  108 x 72 x 54, six FP32 loads, run-time -> compile-time plan: x 37 ->
+// 24 and 39 -> 28 us, y 38 -> 17, z 83 (with the enriched residual) -> 28; one FP64
+// load: x 23 -> 16 and 27 -> 17, y 19 -> 14 and 20 -> 16, z 46 -> 17; 24 x 18 x 12:
+// x 17 -> 11, y 8.4 -> 7.6, z 18 -> 8.4.  The limit of 256 bounds the code size;
+// beyond it a line no longer shares a workgroup with many others.
+#define FFT_LENGTHS(F) \
+    F(12) F(16) F(18) F(24) F(32) F(36) F(48) F(54) F(64) F(72) F(96) F(108) F(128) F(144) F(162) F(192) F(216) F(256)
+static bool ztmpl_size(int n) {
+#define FFT_CASE(N) case N:
+    switch (n) { FFT_LENGTHS(FFT_CASE) return true; default: return false; }
+#undef FFT_CASE
+}
 
 template <typename T> static bool plane_path(const Geometry &g) {
     return g.n0 == g.n1 && plane_size(g.n0) &&
@@ -1005,10 +1027,10 @@ template <typename T> static void set_spec_layout(const xfft_problem *p, FftArgs
 }
 // kx columns per z-pass workgroup: 3 x TK lines of n2 complex values in LDS
 // (about 50 KB, three workgroups per CU)
-template <typename T> static constexpr int tkz_t(int n2) { return (sizeof(T) == 8 ? 8 : 16) / (n2 >= 256 ? 2 : 1); }
+template <typename T> static constexpr int tkz_t(int n2) { return (sizeof(T) == 8 ? 8 : 16) / (n2 > 144 ? 2 : 1); }
 // the alternative tile: twice the columns at n2 = 256 (128-byte runs in FP32,
 // one or two workgroups per CU), half of them below (more workgroups per CU)
-template <typename T> static constexpr int tkz_alt(int n2) { return n2 >= 256 ? 2 * tkz_t<T>(n2) : tkz_t<T>(n2) / 2; }
+template <typename T> static constexpr int tkz_alt(int n2) { return n2 > 144 ? 2 * tkz_t<T>(n2) : tkz_t<T>(n2) / 2; }
 
 // The generic passes run every line of a workgroup through lds_fft, which
 // handles at most MAXB * threads butterflies per stage, and hold their lines
@@ -1118,27 +1140,28 @@ static void zpass(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, con
 // compile-time x and y passes (ztmpl sizes); return false when n has no such variant
 template <typename T, int N> static void xfwd_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                                 const cpx<T> *tw, T *f, const T *z, cpx<T> *spec) {
-    const size_t lds = (size_t)XCfg<N>::PP * XCfg<N>::LS * sizeof(cpx<T>);
+    const size_t lds = (size_t)XCfg<T, N>::PP * XCfg<T, N>::LS * sizeof(cpx<T>);
     static bool init = false;
     if (!init) { allow_lds(k_fft_x_fwd_t<T, N>, lds); init = true; }
     const int64_t npairs = (int64_t)3 * p->g.n2 * p->g.n1 / 2;
-    const int64_t nblk = (npairs + XCfg<N>::PP - 1) / XCfg<N>::PP;
+    const int64_t nblk = (npairs + XCfg<T, N>::PP - 1) / XCfg<T, N>::PP;
     k_fft_x_fwd_t<T, N><<<(unsigned)(nblk * nrhs), 256, lds, s>>>(A, tw, f, z, spec, nrhs);
 }
 template <typename T, int N> static void xinv_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                                 const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u,
                                                 T *d) {
-    const size_t lds = (size_t)XCfg<N>::PP * XCfg<N>::LS * sizeof(cpx<T>);
+    const size_t lds = (size_t)XCfg<T, N>::PP * XCfg<T, N>::LS * sizeof(cpx<T>);
     static bool init = false;
     if (!init) { allow_lds(k_fft_x_inv_t<T, N>, lds); init = true; }
     const int64_t npairs = (int64_t)3 * p->g.n2 * p->g.n1 / 2;
-    const int64_t nblk = (npairs + XCfg<N>::PP - 1) / XCfg<N>::PP;
+    const int64_t nblk = (npairs + XCfg<T, N>::PP - 1) / XCfg<T, N>::PP;
     k_fft_x_inv_t<T, N><<<(unsigned)(nblk * nrhs), 256, lds, s>>>(A, tw, spec, mode, out, u, d, nrhs);
 }
 template <typename T, int N1, bool INV> static void ypass_t(const xfft_problem *p, FftArgs A, int nrhs,
                                                            hipStream_t s, const cpx<T> *tw, cpx<T> *spec) {
-    constexpr int TK = N1 >= 256 ? 8 : 16;
-    const size_t lds = (size_t)TK * fft_ls(N1) * sizeof(cpx<T>);
+    // about 2048 elements per workgroup
+    constexpr int TK = N1 >= 256 ? 8 : N1 >= 96 ? 16 : N1 >= 36 ? 32 : 64;
+    const size_t lds = (size_t)TK * lds_ls<TK >= 32 && (N1 & (N1 - 1)) != 0>(N1) * sizeof(cpx<T>);
     static bool init = false;
     if (!init) { allow_lds(k_fft_y_t<T, N1, TK, INV>, lds); init = true; }
     const int ntiles = (p->g.nh + TK - 1) / TK;
@@ -1148,39 +1171,27 @@ template <typename T, int N1, bool INV> static void ypass_t(const xfft_problem *
 template <typename T> static bool x_forward_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                               const cpx<T> *tw, T *f, const T *z, cpx<T> *spec) {
     switch (p->g.n0) {
-        case 16: xfwd_t<T, 16>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 32: xfwd_t<T, 32>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 48: xfwd_t<T, 48>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 64: xfwd_t<T, 64>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 96: xfwd_t<T, 96>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 128: xfwd_t<T, 128>(p, A, nrhs, s, tw, f, z, spec); return true;
-        case 256: xfwd_t<T, 256>(p, A, nrhs, s, tw, f, z, spec); return true;
+#define FFT_CASE(N) case N: xfwd_t<T, N>(p, A, nrhs, s, tw, f, z, spec); return true;
+        FFT_LENGTHS(FFT_CASE)
+#undef FFT_CASE
         default: return false;
     }
 }
 template <typename T> static bool x_inverse_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                               const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u, T *d) {
     switch (p->g.n0) {
-        case 16: xinv_t<T, 16>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 32: xinv_t<T, 32>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 48: xinv_t<T, 48>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 64: xinv_t<T, 64>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 96: xinv_t<T, 96>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 128: xinv_t<T, 128>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
-        case 256: xinv_t<T, 256>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
+#define FFT_CASE(N) case N: xinv_t<T, N>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
+        FFT_LENGTHS(FFT_CASE)
+#undef FFT_CASE
         default: return false;
     }
 }
 template <typename T, bool INV> static bool y_pass_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                                      const cpx<T> *tw, cpx<T> *spec) {
     switch (p->g.n1) {
-        case 16: ypass_t<T, 16, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 32: ypass_t<T, 32, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 48: ypass_t<T, 48, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 64: ypass_t<T, 64, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 96: ypass_t<T, 96, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 128: ypass_t<T, 128, INV>(p, A, nrhs, s, tw, spec); return true;
-        case 256: ypass_t<T, 256, INV>(p, A, nrhs, s, tw, spec); return true;
+#define FFT_CASE(N) case N: ypass_t<T, N, INV>(p, A, nrhs, s, tw, spec); return true;
+        FFT_LENGTHS(FFT_CASE)
+#undef FFT_CASE
         default: return false;
     }
 }
@@ -1200,12 +1211,12 @@ void launch_green_forward(xfft_problem *p, Work<T> &w, const Tables<T> &tb, T *f
         sy = (int64_t)g.n2 * g.nh;
         xfft_prof_mark(p, -1, s);
         switch (g.n0) {
-            case 16: plane_fwd<T, 16>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
-            case 32: plane_fwd<T, 32>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
-            case 48: plane_fwd<T, 48>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
-            case 64: plane_fwd<T, 64>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
-            case 96: plane_fwd<T, 96>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
-            default: plane_fwd<T, 128>(p, A, nrhs, s, tb.tws[0], f, z, w.spec); break;
+            case 16: plane_fwd<T, 16>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
+            case 32: plane_fwd<T, 32>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
+            case 48: plane_fwd<T, 48>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
+            case 64: plane_fwd<T, 64>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
+            case 96: plane_fwd<T, 96>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
+            default: plane_fwd<T, 128>(p, A, nrhs, s, tb.twp, f, z, w.spec); break;
         }
         xfft_prof_mark(p, K_FFT_X_FWD + (sizeof(T) == 8 ? K_COUNT : 0), s);
     } else {
@@ -1237,13 +1248,10 @@ void launch_green_forward(xfft_problem *p, Work<T> &w, const Tables<T> &tb, T *f
         xfft_prof_mark(p, -1, s);
         if (ztmpl_size(g.n2)) {
             switch (g.n2) {
-                case 16: zpass<T, 16>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                case 32: zpass<T, 32>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                case 48: zpass<T, 48>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                case 64: zpass<T, 64>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                case 96: zpass<T, 96>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                case 128: zpass<T, 128>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
-                default: zpass<T, 256>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
+#define FFT_CASE(N) case N: zpass<T, N>(p, A, nrhs, s, tb, w.spec, sz, sy, E); break;
+                FFT_LENGTHS(FFT_CASE)
+#undef FFT_CASE
+                default: break;
             }
         } else {
             const int tk = tk_z(g);
@@ -1276,12 +1284,12 @@ void launch_green_inverse(xfft_problem *p, Work<T> &w, const Tables<T> &tb, int 
     xfft_prof_mark(p, -1, s);
     if (use_plane<T>(p)) {
         switch (g.n0) {
-            case 16: plane_inv<T, 16>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
-            case 32: plane_inv<T, 32>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
-            case 48: plane_inv<T, 48>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
-            case 64: plane_inv<T, 64>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
-            case 96: plane_inv<T, 96>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
-            default: plane_inv<T, 128>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E); break;
+            case 16: plane_inv<T, 16>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
+            case 32: plane_inv<T, 32>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
+            case 48: plane_inv<T, 48>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
+            case 64: plane_inv<T, 64>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
+            case 96: plane_inv<T, 96>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
+            default: plane_inv<T, 128>(p, A, nrhs, s, tb.twp, w.spec, mode, out, w.u, w.d, E); break;
         }
         E.mode = 0;
     } else {

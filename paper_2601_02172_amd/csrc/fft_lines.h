@@ -1,4 +1,5 @@
-// Compile-time LDS Stockham FFT of up to NL lines of length N (radices 16, 8, 4, 2, 3).
+// Compile-time LDS Stockham FFT of up to NL lines of length N = 2^a 3^b (radices
+// 16, 12, 9, 8, 6, 4, 3, 2).
 //
 // Every stage a thread loads the R inputs of up to MB butterflies, applies the
 // twiddles exp(-+2 pi i r k / (Ns R)) (stage-major table tw, see
@@ -33,12 +34,27 @@ __host__ __device__ constexpr int fft_ls(int n) { return ((n + (n >> 4)) | 1); }
 template <bool ILV> __host__ __device__ constexpr int lds_ls(int n) { return ILV ? (n | 1) : fft_ls(n); }
 template <bool ILV> __host__ __device__ constexpr int lds_pos(int e) { return ILV ? e : fft_pad(e); }
 
-__host__ __device__ constexpr int fft_radix(int n, int stage) {
-    int a = 0, m = n;
+// narrow: an odd factor 3 stays a stage of its own.  The FP64 xy-plane kernels
+// take that plan: 1024 threads share few lines there, and radix 12 leaves most of
+// them idle (96^2 planes, forward, six loads: 148 us with 8 x 12, 116 us with
+// 8 x 4 x 3; in FP32 60 against 65 us, the z pass of 96 in FP64 104 against 129 us).
+__host__ __device__ constexpr int fft_radix(int n, int stage, bool narrow = false) {
+    int a = 0, b = 0, m = n;
     while (m % 2 == 0) { m /= 2; ++a; }
-    const bool use16 = (a + 3) / 4 < (a + 2) / 3;
+    while (m % 3 == 0) { m /= 3; ++b; }
+    if (m != 1) return 0;
     int r[16] = {};
-    int ns = 0;
+    int ns = 0, last = 0;
+    if (b % 2 == 1) {                        // the odd factor 3
+        // with a 4 or a 2 where the rest still takes no more stages
+        const int a2 = a >= 2 ? a - 2 : a, a1 = a >= 1 ? a - 1 : a;
+        const int s0 = a == 0 ? 0 : ((a + 3) / 4), s2 = a2 == 0 ? 0 : ((a2 + 3) / 4), s1 = a1 == 0 ? 0 : ((a1 + 3) / 4);
+        if (narrow) last = 3;
+        else if (a >= 2 && s2 <= s0) { last = 12; a -= 2; }
+        else if (a >= 1 && s1 <= s0) { last = 6; a -= 1; }
+        else last = 3;
+    }
+    const bool use16 = (a + 3) / 4 < (a + 2) / 3;
     if (use16) {
         for (int i = 0; i < a / 4; ++i) r[ns++] = 16;
         if (a % 4 == 3) r[ns++] = 8;
@@ -49,7 +65,8 @@ __host__ __device__ constexpr int fft_radix(int n, int stage) {
         if (a % 3 == 2) r[ns++] = 4;
         if (a % 3 == 1) r[ns++] = 2;
     }
-    while (m % 3 == 0) { m /= 3; r[ns++] = 3; }
+    for (int i = 0; i < b / 2; ++i) r[ns++] = 9;
+    if (last) r[ns++] = last;
     return stage < ns ? r[stage] : 0;
 }
 
@@ -59,10 +76,10 @@ __host__ __device__ constexpr int fft_radix(int n, int stage) {
 // butterfly addresses them with one base and constant offsets.  Entry e
 // (0 <= e < n - 1) equals exp(-2 pi i t / n) with the t returned here (-1 when
 // n has no compile-time plan).
-__host__ __device__ constexpr int fft_stage_index(int n, int e) {
+__host__ __device__ constexpr int fft_stage_index(int n, int e, bool narrow = false) {
     int ns = 1;
     for (int st = 0;; ++st) {
-        const int R = fft_radix(n, st);
+        const int R = fft_radix(n, st, narrow);
         if (R == 0) return -1;
         if (e < ns * R - 1) {
             const int off = e - (ns - 1), k = off / (R - 1), r = off % (R - 1) + 1;
@@ -88,6 +105,35 @@ __device__ __forceinline__ cpx<T> rot16(cpx<T> x) {
         const T c = (T)cs[m], s = (T)sn[m];
         return INV ? cpx<T>{x.x * c - x.y * s, x.y * c + x.x * s} : cpx<T>{x.x * c + x.y * s, x.y * c - x.x * s};
     }
+}
+
+// x * exp(-+2 pi i M / 36) for the multiples M of 3 and 4 that radices 9, 6 and 12 need
+template <typename T, bool INV, int M>
+__device__ __forceinline__ cpx<T> rot36(cpx<T> x) {
+    constexpr double c40 = 0.76604444311897803520, s40 = 0.64278760968653932632;
+    constexpr double c80 = 0.17364817766693034885, s80 = 0.98480775301220805937;
+    constexpr double c160 = -0.93969262078590838405, s160 = 0.34202014332566873304;
+    constexpr double h = 0.86602540378443864676;
+    static_assert(M == 0 || M == 3 || M == 4 || M == 6 || M == 8 || M == 9 || M == 12 || M == 16 || M == 18, "angle");
+    if constexpr (M == 0) return x;
+    else if constexpr (M == 9) return INV ? cpx<T>{-x.y, x.x} : cpx<T>{x.y, -x.x};
+    else if constexpr (M == 18) return {-x.x, -x.y};
+    else {
+        const T c = (T)(M == 4 ? c40 : M == 8 ? c80 : M == 16 ? c160 : M == 3 ? h : M == 6 ? 0.5 : -0.5);
+        const T s = (T)(M == 4 ? s40 : M == 8 ? s80 : M == 16 ? s160 : M == 3 ? 0.5 : h);
+        return INV ? cpx<T>{x.x * c - x.y * s, x.y * c + x.x * s} : cpx<T>{x.x * c + x.y * s, x.y * c - x.x * s};
+    }
+}
+
+template <typename T, bool INV>
+__device__ __forceinline__ void dft3(cpx<T> &x0, cpx<T> &x1, cpx<T> &x2) {
+    const T c = (T)0.86602540378443864676;
+    const cpx<T> t1 = cadd(x1, x2), t2 = csub(x1, x2);
+    const cpx<T> m = {x0.x - (T)0.5 * t1.x, x0.y - (T)0.5 * t1.y};
+    const cpx<T> it2 = INV ? cpx<T>{-c * t2.y, c * t2.x} : cpx<T>{c * t2.y, -c * t2.x};
+    x0 = cadd(x0, t1);
+    x1 = cadd(m, it2);
+    x2 = csub(m, it2);
 }
 
 template <typename T, bool INV>
@@ -153,15 +199,58 @@ __device__ __forceinline__ void dft_small(cpx<T> (&v)[16]) {
         v[6] = csub(e2, w2o);
         v[3] = cadd(e3, w3o);
         v[7] = csub(e3, w3o);
+    } else if constexpr (R == 9) {
+        // 9 = 3 x 3: length-3 DFTs over n1 (n = n2 + 3 n1), twiddles w9^(n2 k1),
+        // length-3 DFTs over n2; output k = k1 + 3 k2
+        dft3<T, INV>(v[0], v[3], v[6]);
+        dft3<T, INV>(v[1], v[4], v[7]);
+        dft3<T, INV>(v[2], v[5], v[8]);
+        v[4] = rot36<T, INV, 4>(v[4]);
+        v[7] = rot36<T, INV, 8>(v[7]);
+        v[5] = rot36<T, INV, 8>(v[5]);
+        v[8] = rot36<T, INV, 16>(v[8]);
+        dft3<T, INV>(v[0], v[1], v[2]);
+        dft3<T, INV>(v[3], v[4], v[5]);
+        dft3<T, INV>(v[6], v[7], v[8]);
+        // v[3 k1 + k2] holds output k1 + 3 k2
+        cpx<T> t = v[1]; v[1] = v[3]; v[3] = t;
+        t = v[2]; v[2] = v[6]; v[6] = t;
+        t = v[5]; v[5] = v[7]; v[7] = t;
+    } else if constexpr (R == 6) {
+        // 6 = 2 x 3: length-2 DFTs over n1 (n = n2 + 3 n1), twiddles w6^n2,
+        // length-3 DFTs over n2; output k = k1 + 2 k2
+        cpx<T> a[3], b[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) { a[i] = cadd(v[i], v[i + 3]); b[i] = csub(v[i], v[i + 3]); }
+        b[1] = rot36<T, INV, 6>(b[1]);
+        b[2] = rot36<T, INV, 12>(b[2]);
+        dft3<T, INV>(a[0], a[1], a[2]);
+        dft3<T, INV>(b[0], b[1], b[2]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) { v[2 * i] = a[i]; v[2 * i + 1] = b[i]; }
+    } else if constexpr (R == 12) {
+        // 12 = 4 x 3: length-4 DFTs over n1 (n = n2 + 3 n1), twiddles w12^(n2 k1),
+        // length-3 DFTs over n2; output k = k1 + 4 k2
+        cpx<T> y[3][4];
+#pragma unroll
+        for (int n2 = 0; n2 < 3; ++n2) {
+#pragma unroll
+            for (int n1 = 0; n1 < 4; ++n1) y[n2][n1] = v[n2 + 3 * n1];
+            dft4<T, INV>(y[n2][0], y[n2][1], y[n2][2], y[n2][3]);
+        }
+        y[1][1] = rot36<T, INV, 3>(y[1][1]);
+        y[1][2] = rot36<T, INV, 6>(y[1][2]);
+        y[1][3] = rot36<T, INV, 9>(y[1][3]);
+        y[2][1] = rot36<T, INV, 6>(y[2][1]);
+        y[2][2] = rot36<T, INV, 12>(y[2][2]);
+        y[2][3] = rot36<T, INV, 18>(y[2][3]);
+#pragma unroll
+        for (int k1 = 0; k1 < 4; ++k1) {
+            dft3<T, INV>(y[0][k1], y[1][k1], y[2][k1]);
+            v[k1] = y[0][k1]; v[k1 + 4] = y[1][k1]; v[k1 + 8] = y[2][k1];
+        }
     } else {
-        const T c = (T)0.86602540378443864676;
-        const cpx<T> a = v[0];
-        const cpx<T> t1 = cadd(v[1], v[2]), t2 = csub(v[1], v[2]);
-        const cpx<T> m = {a.x - (T)0.5 * t1.x, a.y - (T)0.5 * t1.y};
-        const cpx<T> it2 = INV ? cpx<T>{-c * t2.y, c * t2.x} : cpx<T>{c * t2.y, -c * t2.x};
-        v[0] = cadd(a, t1);
-        v[1] = cadd(m, it2);
-        v[2] = csub(m, it2);
+        dft3<T, INV>(v[0], v[1], v[2]);
     }
 }
 
@@ -171,10 +260,10 @@ __device__ __forceinline__ void dft_small(cpx<T> (&v)[16]) {
 // one LDS address and the R accesses use constant offsets.
 template <int M> __host__ __device__ constexpr int pad_step(int r) { return r * M + ((r * M) >> 4); }
 
-template <typename T, int N, int NL, int NT, bool INV, bool ILV = false, int STAGE = 0, int NS = 1>
+template <typename T, int N, int NL, int NT, bool INV, bool ILV = false, bool NARROW = false, int STAGE = 0, int NS = 1>
 __device__ __forceinline__ void fft_lines(cpx<T> *buf, const cpx<T> *__restrict__ tw, int nl = NL,
                                           int tid = threadIdx.x) {
-    constexpr int R = fft_radix(N, STAGE);
+    constexpr int R = fft_radix(N, STAGE, NARROW);
     if constexpr (R != 0) {
         constexpr int LS = lds_ls<ILV>(N);
         constexpr int NB = N / R;
@@ -242,7 +331,7 @@ __device__ __forceinline__ void fft_lines(cpx<T> *buf, const cpx<T> *__restrict_
             }
         }
         __syncthreads();
-        fft_lines<T, N, NL, NT, INV, ILV, STAGE + 1, NS * R>(buf, tw, nl, tid);
+        fft_lines<T, N, NL, NT, INV, ILV, NARROW, STAGE + 1, NS * R>(buf, tw, nl, tid);
     }
 }
 

@@ -69,7 +69,7 @@ extern "C" int xfft_apply_operator_noalloc(xfft_problem *p, const double *x_dev,
     if (p->prof_on) return XFFT_EINVAL;          // the profiling hook creates events
     if (p->device < 0 || p->device >= MAX_DEVICES) return XFFT_EDEVICE;
     const Geometry &g = p->g;
-    const size_t part_bytes = sizeof(double) * NPART * (size_t)p->nslots;
+    const size_t part_bytes = sizeof(double) * NPART * (size_t)p->slots.grn0;   // the operator's slots
     const size_t part_off = 0;
     const size_t cut_off = (part_bytes + 255) & ~(size_t)255;
     const size_t cut_bytes = sizeof(double) * 48 * (size_t)cut_rows(g.nirr);

@@ -433,11 +433,12 @@ __global__ void k_fft_tables(int n, double2 *tw64, float2 *tw32, double *half64,
 
 // stage-major twiddle tables (gathered from the natural-order ones, so the
 // values are identical)
-__global__ void k_fft_stage_tables(int n, const double2 *tw64, const float2 *tw32, double2 *st64, float2 *st32) {
+__global__ void k_fft_stage_tables(int n, const double2 *tw64, const float2 *tw32, double2 *st64, float2 *st32,
+                                   bool narrow64) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= n) return;
-    const int t = e < n - 1 ? fft_stage_index(n, e) : -1;
-    st64[e] = t >= 0 ? tw64[t] : make_double2(1.0, 0.0);
+    const int t = e < n - 1 ? fft_stage_index(n, e) : -1, t64 = narrow64 && e < n - 1 ? fft_stage_index(n, e, true) : t;
+    st64[e] = t64 >= 0 ? tw64[t64] : make_double2(1.0, 0.0);
     st32[e] = t >= 0 ? tw32[t] : make_float2(1.0f, 0.0f);
 }
 
@@ -627,7 +628,16 @@ int compute_tables(xfft_problem *p) {
                                                         p->t32.half[a]);
         k_fft_stage_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(
             n[a], reinterpret_cast<const double2 *>(p->t64.tw[a]), reinterpret_cast<const float2 *>(p->t32.tw[a]),
-            reinterpret_cast<double2 *>(p->t64.tws[a]), reinterpret_cast<float2 *>(p->t32.tws[a]));
+            reinterpret_cast<double2 *>(p->t64.tws[a]), reinterpret_cast<float2 *>(p->t32.tws[a]), false);
+        if (a == 0) {
+            // the xy-plane kernels take the narrow plan in FP64
+            if (hipMalloc(&p->t64.twp, sizeof(cpx<double>) * n[a]) != hipSuccess ||
+                hipMalloc(&p->t32.twp, sizeof(cpx<float>) * n[a]) != hipSuccess)
+                return XFFT_ENOMEM_INTERNAL;
+            k_fft_stage_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(
+                n[a], reinterpret_cast<const double2 *>(p->t64.tw[a]), reinterpret_cast<const float2 *>(p->t32.tw[a]),
+                reinterpret_cast<double2 *>(p->t64.twp), reinterpret_cast<float2 *>(p->t32.twp), true);
+        }
     }
     const int np = p->g.nphase;
     if (hipMalloc(&p->t64.lame, sizeof(double) * 2 * np) != hipSuccess ||
