@@ -139,7 +139,7 @@ __global__ __launch_bounds__(256) void k_enr_final(EnrFin<T> E, const Flags *fla
     const int r = blockIdx.y;
     if (flags && !flags[r].active[parity]) return;
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    enr_final_rows<T>(E, scal, r, j, E.nX);
+    enr_final_rows<T>(E, scal, r, j, E.nX, E.nX);
 }
 
 // iterative refinement: w32.f <- (float) w64.f, w32.u <- 0 for RHS whose outer loop runs

@@ -61,13 +61,13 @@ template <typename T> struct EnrFin {
     const T *fe = nullptr;
 };
 
-// Nodes j0, j0 + stride, ... of load r.
+// Nodes j0, j0 + stride, ... below end of load r.
 template <typename T>
 __device__ __forceinline__ void enr_final_rows(const EnrFin<T> &E, const Scalars *scal, int r, int64_t j0,
-                                               int64_t stride) {
+                                               int64_t stride, int64_t end) {
     const int64_t nX = E.nX;
     const T alpha = (T)scal[r].alpha, beta = (T)scal[r].beta;
-    for (int64_t j = j0; j < nX; j += stride) {
+    for (int64_t j = j0; j < end; j += stride) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int64_t o = (int64_t)r * 3 * nX + c * nX + j;

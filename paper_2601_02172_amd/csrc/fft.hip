@@ -378,13 +378,15 @@ __global__ __launch_bounds__(256) void k_fft_x_inv(FftArgs A, FftPlan pl, const 
 // Used when the xy plane does not fit in LDS (e.g. 256^2): the x transform on
 // PP row pairs per workgroup, the y transform on runs of kx columns; both with
 // the LDS Stockham transform of fft_lines.h.  Spectrum layout [c][kz][ky][kx].
-// Row pairs per workgroup: about 32 KB of LDS; half of it from 256 on (8 pairs in
-// FP32), which keeps twice the workgroups per CU.  Lengths with a factor 3 take
+// Row pairs per workgroup: 2048 elements (17 KB of LDS in FP32), which keeps more
+// workgroups per CU and gives small grids more of them (4096 elements: forward x
+// pass at 24 x 18 x 12, six FP32 loads, 15.3 instead of 10.5 us, 48 x 96 x 72 23.3
+// instead of 19.1, 128^3 equal).  Lengths with a factor 3 take
 // the interleaved layout where a workgroup holds at least 32 lines: its LDS
 // offsets are compile-time constants for every length.
 template <typename T, int N> struct XCfg {
     static constexpr int NH = N / 2 + 1;
-    static constexpr int PP = (N >= 256 ? 2048 : sizeof(T) == 8 && (N & (N - 1)) ? 2048 : 4096) / N;
+    static constexpr int PP = 2048 / N;
     static constexpr bool ILV = PP >= 32 && (N & (N - 1)) != 0;
     static constexpr int LS = lds_ls<ILV>(N);
     static __device__ __forceinline__ int pos(int e) { return lds_pos<ILV>(e); }
@@ -448,13 +450,21 @@ __global__ __launch_bounds__(256) void k_fft_x_fwd_t(FftArgs A, const cpx<T> *tw
 // mode 0: out = G f; mode 1: u += alpha d, d = G f + beta d; mode 2: d = G f
 template <typename T, int N>
 __global__ __launch_bounds__(256) void k_fft_x_inv_t(FftArgs A, const cpx<T> *tw, const cpx<T> *spec, int mode,
-                                                      T *out, T *u, T *d, int nrhs) {
+                                                      T *out, T *u, T *d, int nrhs, EnrFin<T> E, int enr_blocks) {
     using C = XCfg<T, N>;
     extern __shared__ unsigned char smem_raw[];
     cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
     const int64_t npairs = (int64_t)3 * A.n2 * A.n1 / 2;
     const int nblk = (int)((npairs + C::PP - 1) / C::PP);
-    const int64_t lb = xcd_remap(blockIdx.x, gridDim.x);
+    const int64_t nx = (int64_t)nblk * nrhs;
+    if ((int64_t)blockIdx.x >= nx) {
+        // workgroups after the transforms: enriched direction update
+        const int e = (int)(blockIdx.x - nx), re = e / enr_blocks;
+        if (active_rhs(A, re))
+            enr_final_rows<T>(E, A.scal, re, (int64_t)(e - re * enr_blocks) * 256 + threadIdx.x, (int64_t)enr_blocks * 256, E.nX);
+        return;
+    }
+    const int64_t lb = xcd_remap(blockIdx.x, nx);
     const int r = (int)(lb / nblk), blk = (int)(lb % nblk);
     if (!active_rhs(A, r)) return;
     const cpx<T> *sr = spec + (int64_t)r * 3 * A.specN;
@@ -742,11 +752,18 @@ __global__ __launch_bounds__(1024) void k_fft_plane_inv(FftArgs A, const cpx<T> 
     extern __shared__ unsigned char smem_raw[];
     cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
     int tid = threadIdx.x;
+    // Enriched direction update, a node per thread: one load's share of NT nodes per
+    // workgroup, in the first workgroups of the launch (consecutive ones sit on
+    // different XCDs and share the first round).  Per launch: as a loop over all
+    // loads in every workgroup 16^3 FP64 six loads 16.5 us, now 10.2; by shares of a
+    // load's own workgroups 128^3 FP32 138 us and one FP64 load 74 us.
     if (E.mode) {
-        // enriched direction update, spread over the whole grid
-        for (int r = 0; r < nrhs; ++r)
-            if (active_rhs(A, r))
-                enr_final_rows<T>(E, A.scal, r, (int64_t)blockIdx.x * C::NT + tid, (int64_t)gridDim.x * C::NT);
+        const int per = (int)((E.nX + C::NT - 1) / C::NT);
+        for (int e = (int)blockIdx.x; e < per * nrhs; e += (int)gridDim.x) {
+            const int re = e / per;
+            if (active_rhs(A, re))
+                enr_final_rows<T>(E, A.scal, re, (int64_t)(e - re * per) * C::NT + tid, E.nX, E.nX);
+        }
     }
     const int per_r = 3 * A.n2;
     const int q = (int)xcd_remap(blockIdx.x, gridDim.x);
@@ -1149,13 +1166,15 @@ template <typename T, int N> static void xfwd_t(const xfft_problem *p, FftArgs A
 }
 template <typename T, int N> static void xinv_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                                 const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u,
-                                                T *d) {
+                                                T *d, const EnrFin<T> &E) {
     const size_t lds = (size_t)XCfg<T, N>::PP * XCfg<T, N>::LS * sizeof(cpx<T>);
     static bool init = false;
     if (!init) { allow_lds(k_fft_x_inv_t<T, N>, lds); init = true; }
     const int64_t npairs = (int64_t)3 * p->g.n2 * p->g.n1 / 2;
     const int64_t nblk = (npairs + XCfg<T, N>::PP - 1) / XCfg<T, N>::PP;
-    k_fft_x_inv_t<T, N><<<(unsigned)(nblk * nrhs), 256, lds, s>>>(A, tw, spec, mode, out, u, d, nrhs);
+    // four enriched nodes per thread
+    const int eb = E.mode ? (int)((p->g.nX + 1023) / 1024) : 0;
+    k_fft_x_inv_t<T, N><<<(unsigned)((nblk + eb) * nrhs), 256, lds, s>>>(A, tw, spec, mode, out, u, d, nrhs, E, eb);
 }
 template <typename T, int N1, bool INV> static void ypass_t(const xfft_problem *p, FftArgs A, int nrhs,
                                                            hipStream_t s, const cpx<T> *tw, cpx<T> *spec) {
@@ -1178,9 +1197,10 @@ template <typename T> static bool x_forward_t(const xfft_problem *p, FftArgs A, 
     }
 }
 template <typename T> static bool x_inverse_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
-                                              const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u, T *d) {
+                                              const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u, T *d,
+                                              const EnrFin<T> &E) {
     switch (p->g.n0) {
-#define FFT_CASE(N) case N: xinv_t<T, N>(p, A, nrhs, s, tw, spec, mode, out, u, d); return true;
+#define FFT_CASE(N) case N: xinv_t<T, N>(p, A, nrhs, s, tw, spec, mode, out, u, d, E); return true;
         FFT_LENGTHS(FFT_CASE)
 #undef FFT_CASE
         default: return false;
@@ -1297,7 +1317,9 @@ void launch_green_inverse(xfft_problem *p, Work<T> &w, const Tables<T> &tb, int 
         const int64_t npairs = (int64_t)3 * g.n2 * g.n1 / 2;
         dim3 grid((unsigned)((npairs + pp - 1) / pp), nrhs);
         const size_t lds = (size_t)pp * (g.n0 + 1) * sizeof(cpx<T>);
-        if (!x_inverse_t<T>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d))
+        if (x_inverse_t<T>(p, A, nrhs, s, tb.tws[0], w.spec, mode, out, w.u, w.d, E))
+            E.mode = 0;
+        else
             k_fft_x_inv<T><<<grid, 256, lds, s>>>(A, p->plan[0], tb.tw[0], w.spec, mode, out, w.u, w.d, pp);
     }
     xfft_prof_mark(p, K_FFT_X_INV + (sizeof(T) == 8 ? K_COUNT : 0), s);

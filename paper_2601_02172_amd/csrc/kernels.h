@@ -63,7 +63,7 @@ void launch_green_forward(xfft_problem *p, Work<T> &w, const Tables<T> &tb, T *f
 // mode 0: out = P^-1 f (FE part) written to `out`; mode 1: CG update
 // (u += alpha d_old, d = y + beta d_old); mode 2: d = y.  The enriched update
 // of launch_enr_final (enr_mode 1 or 2; 0: none) runs inside the xy-plane
-// kernels when they are used, else as a kernel of its own.
+// kernels or as extra workgroups of the compile-time x pass, else as a kernel of its own.
 template <typename T>
 void launch_green_inverse(xfft_problem *p, Work<T> &w, const Tables<T> &tb, int mode, T *out, int nrhs,
                           const Flags *flags, int parity, hipStream_t s, int enr_mode);
