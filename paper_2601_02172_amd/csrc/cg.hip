@@ -24,6 +24,8 @@ namespace {
 // rounding of the correction, far below this margin
 constexpr double INNER_MARGIN = 0.5;
 
+constexpr int SC_T = 1024;   // threads of the scalar recurrences
+
 struct ScArgs {
     const double *partial;
     int nslots;
@@ -37,39 +39,61 @@ struct ScArgs {
     double *sum_out;      // [rhs][7] or null
 };
 
-__global__ __launch_bounds__(256) void k_scalars(ScArgs A) {
-    __shared__ double red[4 * 7];
+// One workgroup per right-hand side.  NV: partial sums per slot that the operation
+// needs (1: the dot product, 7: with the stress integral).  Bound by latency: the
+// flag, the recurrence's own values and the partial sums are loaded together by
+// 1024 threads.  Per launch (with the events' share), 256 threads summing seven
+// values each -> now: 128^3 FP32 with six loads 11.7 -> 7.5 us, one FP64 load 11.7
+// -> 8.8, 64^3 8.1 -> 6.2 and 8.5 -> 6.9.
+template <int NV>
+__global__ __launch_bounds__(SC_T) void k_scalars(ScArgs A) {
+    __shared__ double red[SC_T / 64 * (NV == 7 ? 8 : 1)];
     const int r = blockIdx.x;
     Flags &F = A.flags[r];
     const bool act = (A.op == SC_ALPHA || A.op == SC_BETA) ? F.active[A.parity] != 0 : true;
+    Scalars S;
+    if (threadIdx.x == 0) S = A.scal[r];
+    const double *P = A.partial + ((int64_t)r * A.nslots + A.s0) * NPART;
+    const double *P1 = A.partial + ((int64_t)r * A.nslots + A.s1) * NPART;
+    // NV = 7: value threadIdx.x % 8 of slots threadIdx.x / 8, ... (whole lines per eight
+    // lanes, one value per lane to reduce instead of seven)
+    static_assert(NPART == 8, "eight values per slot");
+    const int q = NV == 7 ? (int)threadIdx.x & 7 : 0, first = NV == 7 ? (int)threadIdx.x >> 3 : (int)threadIdx.x;
+    constexpr int STEP = NV == 7 ? SC_T / 8 : SC_T;
+    double w = 0.0;
+#pragma unroll 8
+    for (int i = first; i < A.n; i += STEP) w += P[(int64_t)i * NPART + q];
+#pragma unroll 8
+    for (int i = first; i < A.n1; i += STEP) w += P1[(int64_t)i * NPART + q];
     if (!act) {
         // an inactive right-hand side stays inactive in the next iteration too
         if (A.op == SC_BETA && threadIdx.x == 0) F.active[1 - A.parity] = 0;
         return;
     }
-    double v[7] = {0, 0, 0, 0, 0, 0, 0};
-    const double *P = A.partial + ((int64_t)r * A.nslots + A.s0) * NPART;
-    for (int i = threadIdx.x; i < A.n; i += blockDim.x) {
 #pragma unroll
-        for (int q = 0; q < 7; ++q) v[q] += P[(int64_t)i * NPART + q];
-    }
-    const double *P1 = A.partial + ((int64_t)r * A.nslots + A.s1) * NPART;
-    for (int i = threadIdx.x; i < A.n1; i += blockDim.x) {
-#pragma unroll
-        for (int q = 0; q < 7; ++q) v[q] += P1[(int64_t)i * NPART + q];
-    }
-    block_sum<7>(v, red);
+    for (int off = 32; off >= (NV == 7 ? 8 : 1); off >>= 1) w += __shfl_xor(w, off, 64);
+    constexpr int NR = NV == 7 ? 8 : 1, NW = SC_T / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane < NR) red[wave * NR + lane] = w;
+    __syncthreads();
     if (threadIdx.x != 0) return;
-    Scalars &S = A.scal[r];
+    double v[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+        v[k] = 0.0;
+#pragma unroll
+        for (int g = 0; g < NW; ++g) v[k] += red[g * NR + k];
+    }
     if (A.sum_out) {
 #pragma unroll
-        for (int q = 0; q < 7; ++q) A.sum_out[r * 7 + q] = v[q];
+        for (int q = 0; q < 7; ++q) A.sum_out[r * 7 + q] = q < NV ? v[q < NV ? q : 0] : 0.0;
     }
+    auto stress = [&](int q) { return NV == 7 ? v[NV == 7 ? q : 0] : 0.0; };
     const double r2 = 1.41421356237309504880;
     if (A.op == SC_INIT_SIGMA) {
         // Mandel average stress from the stress integral (tensor components)
-        S.sigma[0] = v[1] / A.volume; S.sigma[1] = v[2] / A.volume; S.sigma[2] = v[3] / A.volume;
-        S.sigma[3] = r2 * v[4] / A.volume; S.sigma[4] = r2 * v[5] / A.volume; S.sigma[5] = r2 * v[6] / A.volume;
+        S.sigma[0] = stress(1) / A.volume; S.sigma[1] = stress(2) / A.volume; S.sigma[2] = stress(3) / A.volume;
+        S.sigma[3] = r2 * stress(4) / A.volume; S.sigma[4] = r2 * stress(5) / A.volume; S.sigma[5] = r2 * stress(6) / A.volume;
         S.alpha = 0.0;
         S.beta = 0.0;
     } else if (A.op == SC_INIT_RES) {
@@ -89,6 +113,7 @@ __global__ __launch_bounds__(256) void k_scalars(ScArgs A) {
         if (!(zd > 0.0) || !isfinite(zd)) {
             F.breakdown = 1;
             S.alpha = 0.0;
+            A.scal[r] = S;
             return;
         }
         // step of the scheme (Sec. 3, solvers): linear CG takes the exact line
@@ -102,10 +127,10 @@ __global__ __launch_bounds__(256) void k_scalars(ScArgs A) {
             S.alpha_lag = S.res2 / zd;
         }
         S.alpha = alpha;
-        S.sigma[0] += alpha * v[1] / A.volume; S.sigma[1] += alpha * v[2] / A.volume;
-        S.sigma[2] += alpha * v[3] / A.volume;
-        S.sigma[3] += alpha * r2 * v[4] / A.volume; S.sigma[4] += alpha * r2 * v[5] / A.volume;
-        S.sigma[5] += alpha * r2 * v[6] / A.volume;
+        S.sigma[0] += alpha * stress(1) / A.volume; S.sigma[1] += alpha * stress(2) / A.volume;
+        S.sigma[2] += alpha * stress(3) / A.volume;
+        S.sigma[3] += alpha * r2 * stress(4) / A.volume; S.sigma[4] += alpha * r2 * stress(5) / A.volume;
+        S.sigma[5] += alpha * r2 * stress(6) / A.volume;
     } else if (A.op == SC_BETA) {
         const double rn = v[0];
         // the basic and Barzilai-Borwein schemes step along y = P^-1 f
@@ -123,6 +148,7 @@ __global__ __launch_bounds__(256) void k_scalars(ScArgs A) {
         F.conv = conv ? 1 : 0;
         F.active[1 - A.parity] = (!conv && !F.breakdown && F.iters < A.maxit) ? 1 : 0;
     }
+    A.scal[r] = S;
 }
 
 template <typename T>
@@ -190,7 +216,11 @@ void launch_scalars(xfft_problem *p, int op, int crit, int nrhs, int parity, dou
     A.scheme = p->scheme;
     A.sum_out = sum_out;
     xfft_prof_mark(p, -1, s);
-    k_scalars<<<nrhs, 256, 0, s>>>(A);
+    // the stress integral enters the initial average stress, the sums handed out and, in
+    // criterion 0, the average stress that alpha carries along
+    const bool seven = op == SC_INIT_SIGMA || op == SC_SUM_ONLY || (op == SC_ALPHA && crit == 0);
+    if (seven) k_scalars<7><<<nrhs, SC_T, 0, s>>>(A);
+    else k_scalars<1><<<nrhs, SC_T, 0, s>>>(A);
     xfft_prof_mark(p, K_SCALARS + K_COUNT, s);
 }
 
