@@ -23,15 +23,16 @@ template <typename T> struct EnrUpd {
     int slot0 = 0;
 };
 
-// Workgroup b of load r (blockDim.x == ENR_BLOCK); red holds ENR_BLOCK / 64 doubles.
+// Share b (ENR_BLOCK nodes) of load r by one workgroup; red holds blockDim.x / 64 doubles.
 template <typename T>
 __device__ __forceinline__ void enr_update_block(const EnrUpd<T> &E, const Scalars *scal, double *partial,
                                                  int nslots, int r, int b, double *red) {
     const int64_t nX = E.nX;
-    const int64_t j = (int64_t)b * ENR_BLOCK + threadIdx.x;
     double acc[1] = {0.0};
-    if (j < nX) {
-        const T alpha = (T)scal[r].alpha;
+    const T alpha = (T)scal[r].alpha;
+    for (int t = threadIdx.x; t < ENR_BLOCK; t += blockDim.x) {
+        const int64_t j = (int64_t)b * ENR_BLOCK + t;
+        if (j >= nX) break;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const int64_t o = (int64_t)r * 3 * nX + c * nX + j;

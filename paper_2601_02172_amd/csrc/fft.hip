@@ -975,6 +975,189 @@ void k_fft_z_t(FftArgs A, const cpx<T> *tw, const T *h0, const T *h1,
     }
 }
 
+// ---------------------------------------------------------------- z pass, two register stages
+// For n2 = R1 R2.  Stockham forward with radices R1, R2 and inverse with R2, R1:
+// butterfly j of the second forward stage leaves its outputs at j + r R1, which are
+// the inputs of butterfly j of the first inverse stage, so one thread keeps the
+// three components of those R2 frequencies in registers through the second forward
+// stage, the Green multiply and the first inverse stage; the first forward stage
+// reads global memory into registers and the last inverse one writes it.  A value
+// crosses LDS twice (4 accesses) with three barriers, instead of 12 accesses and
+// ten barriers in k_fft_z_t.  Lane kl of 16 (8 in FP64) takes column kx0 + kl, so
+// every row of a run is one 128-byte access.  Bound: below 128^3 the chain load -
+// barrier - Green - barrier - store of the few workgroups a CU holds, above it the
+// 128-byte runs.  256 threads also where a stage has fewer items, because the
+// enriched workgroups of the same launch need them (128 threads: 14 us instead of
+// 10 at 64^3 FP64).
+constexpr int zp_r1(int n) {
+    for (int r1 : {16, 12, 9, 8, 6, 4})
+        for (int r2 : {16, 12, 9, 8, 6, 4, 3})
+            if (r1 * r2 == n) return r1;
+    return 0;
+}
+// Where it is used; us per launch, k_fft_z_t / k_fft_z2.  FP32, 6 loads: up to a
+// middle radix of 6, whose three components fit five waves per SIMD: n2 = 36
+// 12.7 / 11.1, 54 18 / 15.8, 64 21 / 17, 72 26 / 20.6, 96 47.8 / 47.1; above it the
+// registers leave too few waves (128 101 / 104, 256 812 / 1005).  FP64, 1 and 6 loads:
+// from 96 on up to a middle radix of 9 (96 22.4 / 20.5 and 102 / 102, 108 31.3 / 24.4
+// and 139 / 106, 128 40.6 / 37.6 and 238 / 204) and with a first radix of 16 (64
+// 11.8 / 10.0 and 32.4 / 29.8); not at 54 and 72 (6 loads: 46.5 / 55.5 and
+// 46.7 / 49.4), where half the threads have no item in either stage.
+template <typename T> constexpr bool zp_two(int n) {
+    const int r1 = zp_r1(n);
+    if (r1 == 0) return false;
+    return sizeof(T) == 8 ? n / r1 <= 9 && (n >= 96 || r1 == 16) : n / r1 <= 6;
+}
+template <typename T, int N2, int TK> struct Z2Cfg {
+    static constexpr int R1 = zp_r1(N2) ? zp_r1(N2) : 1, R2 = N2 / R1;
+    static constexpr int S1 = 3 * R2 * TK, S2 = R1 * TK;       // items of the outer stages and of the middle part
+    static constexpr int NT = 256;
+    static constexpr int WV = sizeof(T) == 4 ? 5 : 1;
+    static constexpr int LS = N2 | 1;
+};
+
+template <typename T, int N2, int TK>
+__global__ __launch_bounds__((Z2Cfg<T, N2, TK>::NT)) __attribute__((amdgpu_waves_per_eu(Z2Cfg<T, N2, TK>::WV)))
+void k_fft_z2(FftArgs A, const cpx<T> *tw, const T *h0, const T *h1, const T *h2, cpx<T> *spec, int64_t sz, int64_t sy,
+              int nrhs, EnrUpd<T> E) {
+    using C = Z2Cfg<T, N2, TK>;
+    constexpr int R1 = C::R1, R2 = C::R2, LS = C::LS, NT = C::NT;
+    extern __shared__ unsigned char smem_raw[];
+    cpx<T> *sh = reinterpret_cast<cpx<T> *>(smem_raw);
+    __shared__ double red[8];
+    const int nh = A.nh;
+    const int ntiles = (nh + TK - 1) / TK;
+    const int nblk = A.n1 * ntiles;                 // workgroups per right-hand side
+    const int tk = (nh + ntiles - 1) / ntiles;
+    if ((int)blockIdx.x >= nblk * nrhs) {
+        // enriched residual update (workgroups after the z-pass ones)
+        const int e = (int)blockIdx.x - nblk * nrhs, re = e / E.nblk;
+        if (active_rhs(A, re)) enr_update_block<T>(E, A.scal, A.partial, A.nslots, re, e - re * E.nblk, red);
+        return;
+    }
+    int nact = 0;
+    for (int q = 0; q < nrhs; ++q) nact += active_rhs(A, q) ? 1 : 0;
+    const int total = nact * nblk;
+    if ((int)blockIdx.x >= total) return;
+    const int L = (int)xcd_remap(blockIdx.x, total);
+    int ka = L / nblk;
+    const int blk = L - ka * nblk;
+    int r = 0;
+    while (!active_rhs(A, r) || ka-- > 0) ++r;      // the ka-th active load
+    const int tile = blk % ntiles, ky = blk / ntiles;
+    const int kx0 = tile * tk, ncol = min(tk, nh - kx0);
+    cpx<T> *base = spec + (int64_t)r * 3 * A.specN + (int64_t)ky * sy + kx0;
+    const int tid = threadIdx.x;
+    const int64_t st2 = (int64_t)R2 * sz;
+    // first forward stage: rows j + r R2 -> positions j R1 + r
+#pragma unroll
+    for (int it0 = 0; it0 < C::S1; it0 += NT) {
+        const int it = it0 + tid, kl = it % TK, j = (it / TK) % R2, c = it / (TK * R2);
+        if ((C::S1 % NT == 0 || it < C::S1) && kl < ncol) {
+            const cpx<T> *g = base + (int64_t)c * A.specN + kl + (int64_t)j * sz;
+            cpx<T> v[16];
+#pragma unroll
+            for (int q = 0; q < R1; ++q) v[q] = g[q * st2];
+            dft_small<T, false, R1>(v);
+            cpx<T> *o = sh + (c * tk + kl) * LS + j * R1;
+#pragma unroll
+            for (int q = 0; q < R1; ++q) o[q] = v[q];
+        }
+    }
+    __syncthreads();
+    // middle part: frequencies j + r R1 of the three components
+    constexpr int MI = (C::S2 + NT - 1) / NT;
+    const T scale = (T)(1.0 / ((double)A.n0 * (double)A.n1 * (double)N2));
+    const T s1 = h1[2 * ky], c1 = h1[2 * ky + 1];
+    double part = 0.0;
+    cpx<T> m[MI][3][16];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int it = i * NT + tid, kl = it % TK, j = it / TK;
+        if ((C::S2 % NT == 0 || it < C::S2) && kl < ncol) {
+            cpx<T> w[R2];
+#pragma unroll
+            for (int q = 1; q < R2; ++q) w[q] = tw[q * j];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const cpx<T> *p = sh + (c * tk + kl) * LS + j;
+#pragma unroll
+                for (int q = 0; q < R2; ++q) {
+                    const cpx<T> x = p[q * R1];
+                    m[i][c][q] = q == 0 ? x : cmul(x, w[q == 0 ? 1 : q]);
+                }
+                dft_small<T, false, R2>(m[i][c]);
+            }
+            const int kx = kx0 + kl;
+            const T s0 = h0[2 * kx], c0 = h0[2 * kx + 1];
+            const double wk = (kx == 0 || 2 * kx == A.n0) ? 1.0 : 2.0;
+#pragma unroll
+            for (int q = 0; q < R2; ++q) {
+                const int zz = j + q * R1;
+                cpx<T> fv[3] = {m[i][0][q], m[i][1][q], m[i][2][q]};
+                const cpx<T> f0[3] = {fv[0], fv[1], fv[2]};
+                green_apply<T>(s0, c0, s1, c1, h2[2 * zz], h2[2 * zz + 1], fv, kx == 0 && ky == 0 && zz == 0);
+                double e = 0.0;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    fv[c].x *= scale;
+                    fv[c].y *= scale;
+                    e += (double)f0[c].x * (double)fv[c].x + (double)f0[c].y * (double)fv[c].y;
+                    m[i][c][q] = fv[c];
+                }
+                part += wk * e;
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) dft_small<T, true, R2>(m[i][c]);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        const int it = i * NT + tid, kl = it % TK, j = it / TK;
+        if ((C::S2 % NT == 0 || it < C::S2) && kl < ncol) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                cpx<T> *p = sh + (c * tk + kl) * LS + j * R2;
+#pragma unroll
+                for (int q = 0; q < R2; ++q) p[q] = m[i][c][q];
+            }
+        }
+    }
+    __syncthreads();
+    // last inverse stage: positions j + r R2 -> rows j + r R2
+#pragma unroll
+    for (int it0 = 0; it0 < C::S1; it0 += NT) {
+        const int it = it0 + tid, kl = it % TK, j = (it / TK) % R2, c = it / (TK * R2);
+        if ((C::S1 % NT == 0 || it < C::S1) && kl < ncol) {
+            const cpx<T> *p = sh + (c * tk + kl) * LS + j;
+            cpx<T> v[16];
+#pragma unroll
+            for (int q = 0; q < R1; ++q) {
+                cpx<T> x = p[q * R2];
+                if (q > 0) {
+                    cpx<T> w = tw[q * j];
+                    w.y = -w.y;
+                    x = cmul(x, w);
+                }
+                v[q] = x;
+            }
+            dft_small<T, true, R1>(v);
+            cpx<T> *g = base + (int64_t)c * A.specN + kl + (int64_t)j * sz;
+#pragma unroll
+            for (int q = 0; q < R1; ++q) g[q * st2] = v[q];
+        }
+    }
+    double pv[1] = {part};
+    block_sum<1>(pv, red);
+    if (tid == 0) {
+        double *P = A.partial + ((int64_t)r * A.nslots + A.slot0 + blk) * NPART;
+        P[0] = pv[0];
+#pragma unroll
+        for (int q = 1; q < 7; ++q) P[q] = 0.0;
+    }
+}
+
 template <typename T> int pairs_for(int n0) {
     // limit: butterflies per stage <= MAXB * 256 (radix 2 worst case) and LDS <= 64 KiB
     int p = (MAXB * 256 * 2) / n0;
@@ -1135,15 +1318,21 @@ static void zpass_tk(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, 
                      int64_t sz, int64_t sy, const EnrUpd<T> &E) {
     // LDS holds the 3 tk lines a workgroup uses (tk <= TK columns share the nh
     // columns evenly); at 128^3 in FP32 that is 13 of 16, which lets four
-    // workgroups share a CU (64 registers, eight waves per SIMD)
+    // workgroups of k_fft_z_t share a CU (64 registers, eight waves per SIMD)
     const int nh = p->g.nh, ntiles = (nh + TK - 1) / TK, tk = (nh + ntiles - 1) / ntiles;
-    const size_t line = (size_t)lds_ls<3 * TK >= 32>(N2) * sizeof(cpx<T>);
-    const size_t lds = (size_t)3 * tk * line;
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_z_t<T, N2, TK>, (size_t)3 * TK * line); init = true; }
     const int64_t grid = ((int64_t)p->g.n1 * ntiles + E.nblk) * nrhs;
-    k_fft_z_t<T, N2, TK><<<(unsigned)grid, 512, lds, s>>>(A, tb.tws[2], tb.half[0], tb.half[1], tb.half[2], spec,
-                                                        sz, sy, nrhs, E);
+    static bool init = false;
+    if constexpr (zp_two<T>(N2)) {
+        const size_t line = Z2Cfg<T, N2, TK>::LS * sizeof(cpx<T>);
+        if (!init) { allow_lds(k_fft_z2<T, N2, TK>, (size_t)3 * TK * line); init = true; }
+        k_fft_z2<T, N2, TK><<<(unsigned)grid, Z2Cfg<T, N2, TK>::NT, (size_t)3 * tk * line, s>>>(
+            A, tb.tw[2], tb.half[0], tb.half[1], tb.half[2], spec, sz, sy, nrhs, E);
+    } else {
+        const size_t line = (size_t)lds_ls<3 * TK >= 32>(N2) * sizeof(cpx<T>);
+        if (!init) { allow_lds(k_fft_z_t<T, N2, TK>, (size_t)3 * TK * line); init = true; }
+        k_fft_z_t<T, N2, TK><<<(unsigned)grid, 512, (size_t)3 * tk * line, s>>>(
+            A, tb.tws[2], tb.half[0], tb.half[1], tb.half[2], spec, sz, sy, nrhs, E);
+    }
 }
 template <typename T, int N2>
 static void zpass(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, const Tables<T> &tb, cpx<T> *spec,
