@@ -156,10 +156,18 @@ __device__ __forceinline__ double dpp_row_shr1(double v) {
 // with the same base when tx, ty >= 1.  Node (a, b) collects corner c of the
 // voxels (a - dx, b - dy): corners 0/4 from its own voxel, 1/5 from the thread
 // at tx - 1, 2/6 from ty - 1 and 3/7 from (tx - 1, ty - 1).
+// Bound in FP32: vector issue, 240 instructions a layer and wave of which the six
+// elements need 210; five waves per SIMD (six at 80 registers spill: 256x256x128
+// 117 -> 159 us).  FP64 had two workgroups a CU by LDS; with the row sums in two
+// buffers instead of three it has three (46 KB, 168 registers): one application at
+// 256x256x128 240 -> 197 us; inside a solve at 128^3 400 -> 377 us for six loads and
+// 70.4 -> 69.5 for one.  FP32 inside a solve at 128^3, six loads: 178.5 -> 168.7
+// (moduli a layer ahead, loads in the order of their use, no division in the
+// prologue).
 template <typename T, bool HX, bool EB, bool ST>
-__global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regular(OpArgs<T> A) {
+__global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regular(OpArgs<T> A) {
     __shared__ T Dp[3][TC * TC][3];
-    __shared__ T FB[3][6][TE * TE];    // row sums for the node above, one buffer per layer of the unrolled march
+    __shared__ T FB[2][6][TE * TE];    // row sums for the node above, of this layer and the one before
     __shared__ double red[4 * 7];
 
     // workgroups after the regular ones gather the enriched forces (they only
@@ -171,8 +179,8 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
         return;
     }
     // logical block: (rhs, z chunk, tile y, tile x), x fastest
-    const int64_t lb = xcd_remap(blockIdx.x, nreg);
-    const int r = (int)(lb / A.reg_blocks), blk = (int)(lb % A.reg_blocks);
+    const unsigned lb = (unsigned)xcd_remap(blockIdx.x, nreg);
+    const int r = (int)(lb / (unsigned)A.reg_blocks), blk = (int)(lb - (unsigned)r * (unsigned)A.reg_blocks);
     if (!rhs_active(A, r)) return;
     const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
     const int tile = blk % A.tiles_xy, zc = blk / A.tiles_xy;
@@ -182,10 +190,12 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
     const int n0 = A.n0, n1 = A.n1, n2 = A.n2;
     const int64_t N = A.N, plane_sz = (int64_t)n0 * n1;
     const int a = i0 - 1 + tx, b = j0 - 1 + ty;
-    // tiles may wrap more than once around small grids: full modulo here, once.
+    // a tile can wrap more than once around a grid of fewer than TE nodes: full
+    // modulo there, one wrap otherwise.
     // Offsets are 32-bit from per-load base pointers (3 N values of T and the
     // corner-force buffer of one load stay below 2^32 bytes, checked at setup).
-    const int aw = ((a % n0) + n0) % n0, bw = ((b % n1) + n1) % n1;
+    const auto wrapn = [](int v, int n) { return n >= TE ? wrapi(v, n) : ((v % n) + n) % n; };
+    const int aw = wrapn(a, n0), bw = wrapn(b, n1);
     const uint32_t N32 = (uint32_t)N, psz = (uint32_t)n0 * (uint32_t)n1;
     const uint32_t colv = (uint32_t)aw + (uint32_t)n0 * (uint32_t)bw;
     uint32_t colxy[2];
@@ -193,7 +203,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
     for (int u = 0; u < 2; ++u) {
         const int col = tid + 256 * u;
         const int cx = col % TC, cy = col / TC;
-        const int xi = (((i0 - 1 + cx) % n0) + n0) % n0, yi = (((j0 - 1 + cy) % n1) + n1) % n1;
+        const int xi = wrapn(i0 - 1 + cx, n0), yi = wrapn(j0 - 1 + cy, n1);
         colxy[u] = (uint32_t)xi + (uint32_t)n0 * (uint32_t)yi;
     }
     const bool owner = tx >= 1 && ty >= 1 && a < n0 && b < n1;
@@ -254,13 +264,10 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
     mv[0] = elem(A.vmat, colv + plane_off(k0 - 1));
     mv[1] = (k0 < k1) ? elem(A.vmat, colv + plane_off(k0)) : 0;
     mv[2] = 0;
-    // buffered corner forces of an irregular voxel.  With PF those of the voxel
-    // one layer ahead are loaded a layer before they are used (24 more
-    // registers); without it the FP32 kernel fits five waves per SIMD (86
-    // registers), which hides the load latency better
-    constexpr bool PF = false;
-    T Fn[8][3];
-    auto fetch_cut = [&](int mq) {
+    // buffered corner forces of an irregular voxel, loaded in the layer that uses
+    // them: one layer ahead they would take 24 more registers and a wave per SIMD
+    // away.  Without these loads the kernel would take 8 % less time.
+    auto fetch_cut = [&](int mq, T (&Fn)[8][3]) {
         const uint32_t q = (uint32_t)(-mq - 1);
         T v[24];
 #pragma unroll
@@ -274,7 +281,14 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
 #pragma unroll
             for (int i = 0; i < 3; ++i) Fn[c][i] = v[3 * c + i];
     };
-    if (PF && mv[0] < 0) fetch_cut(mv[0]);
+    // moduli of the voxels at layers kl, kl + 1: loaded one layer before their use
+    T LM[3][2];
+    auto fetch_lame = [&](int mq, T (&dst)[2]) {
+        const uint32_t q = (uint32_t)max(mq, 0);
+        dst[0] = elem(A.lame, 2 * q);
+        dst[1] = elem(A.lame, 2 * q + 1);
+    };
+    fetch_lame(mv[0], LM[0]);
     __syncthreads();
 
     T acc[3] = {0, 0, 0};
@@ -284,19 +298,13 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
         constexpr int sb = decltype(slot_tag)::value, st = (sb + 1) % 3, sn = (sb + 2) % 3;
         const int kl = k0 - 1 + s;
         const bool more = kl + 2 <= k1, more2 = kl + 3 <= k1;
-        if (more2) fetch_plane(kl + 3, R[sb]);
-        mv[sn] = (kl + 2 < k1) ? elem(A.vmat, colv + plane_off(kl + 2)) : 0;
-        const int m = mv[sb], mn = mv[st];
+        const int m = mv[sb];
         const uint32_t vox = colv + plane_off(kl);
         T F[8][3];
-        if (m < 0) {
-            if (!PF) fetch_cut(m);
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-#pragma unroll
-                for (int i = 0; i < 3; ++i) F[c][i] = Fn[c][i];
-        }
-        if (PF && mn < 0) fetch_cut(mn);
+        if (m < 0) fetch_cut(m, F);
+        fetch_lame(mv[st], LM[st]);
+        mv[sn] = (kl + 2 < k1) ? elem(A.vmat, colv + plane_off(kl + 2)) : 0;
+        if (more2) fetch_plane(kl + 3, R[sb]);
         if (m >= 0) {
             T U[8][3];
 #pragma unroll
@@ -307,7 +315,7 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
                 for (int i = 0; i < 3; ++i) U[c][i] = HX ? Dp[sl][col][i] : (T)0;
             }
             const T V = (T)(1.0 / 6.0);
-            const T lamV = V * A.lame[2 * m], muV = V * A.lame[2 * m + 1];
+            const T lamV = V * LM[sb][0], muV = V * LM[sb][1];
             Sym<T> S = sym_acc_zero<T>();
             regular_voxel<T, EB, ST>(U, eb, lamV, muV, F, S);
             if (ST && owner && kl >= k0) {
@@ -324,8 +332,8 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
         for (int i = 0; i < 3; ++i) {
             bot[i] = F[0][i] + dpp_row_shr1(F[1][i]);
             top[i] = F[4][i] + dpp_row_shr1(F[5][i]);
-            FB[sb][i][tid] = F[2][i] + dpp_row_shr1(F[3][i]);
-            FB[sb][3 + i][tid] = F[6][i] + dpp_row_shr1(F[7][i]);
+            FB[s & 1][i][tid] = F[2][i] + dpp_row_shr1(F[3][i]);
+            FB[s & 1][3 + i][tid] = F[6][i] + dpp_row_shr1(F[7][i]);
         }
         T dv[3] = {0, 0, 0};
         if constexpr (HX) {
@@ -333,14 +341,16 @@ __global__ __launch_bounds__(256, (sizeof(T) == 4 && !ST) ? 5 : 1) void k_regula
             for (int i = 0; i < 3; ++i) dv[i] = Dp[sb][tx + TC * ty][i];
         }
         if (more) store_plane(sn, R[sn]);
-        // one barrier per layer: the row sums rotate through three buffers, and
-        // the Dp slot written next layer was last read before this barrier
+        // one barrier per layer: the row sums alternate between two buffers (those
+        // of layer s are read before the barrier of layer s + 1 and overwritten
+        // after it), and the Dp slot written next layer was last read before this
+        // barrier
         __syncthreads();
         if (owner) {
 #pragma unroll
             for (int i = 0; i < 3; ++i) {
-                bot[i] += FB[sb][i][tid - 16];
-                top[i] += FB[sb][3 + i][tid - 16];
+                bot[i] += FB[s & 1][i][tid - 16];
+                top[i] += FB[s & 1][3 + i][tid - 16];
             }
             if (kl >= k0) {
                 T dot = 0;                 // three terms in T, summed over the column in FP64
