@@ -246,11 +246,8 @@ void tune_store(std::map<TuneKey, int> &cache, const TuneKey &key, int value) {
 }
 
 // Choose the regular-voxel operator depth (planes per block) by timing the
-// candidates in the solve's launch configuration.  On the zeros that are timed
-// here a deeper march looks better than on a solve's data (128^3 FP64, one load:
-// 87.8 us at the default depth 8 and 85.9 at 16 here, but 69.5 and 72.2 for the
-// regular kernel inside a solve), so another depth replaces the default only when
-// it is at least 3 % faster.
+// candidates in the solve's launch configuration (FP64 iterations carry the
+// average stress, FP32 ones do not).
 template <typename T>
 int autotune_depth(xfft_problem *p, Work<T> &w, const Tables<T> &tb, int nrhs) {
     static std::map<TuneKey, int> cache;
@@ -266,21 +263,20 @@ int autotune_depth(xfft_problem *p, Work<T> &w, const Tables<T> &tb, int nrhs) {
     hipEvent_t e0, e1;
     HIP_OK(hipEventCreate(&e0));
     HIP_OK(hipEventCreate(&e1));
-    const int kz0 = p->slots.kz;
-    int best = kz0;
+    const bool stress = sizeof(T) == 8;
+    int best = p->slots.kz;
     float best_ms = 1e30f;
-    for (int kz : {kz0, 4, 8, 16, 32}) {
-        if ((kz > p->g.n2 && kz != kz0) || (kz == kz0 && best_ms < 1e30f)) continue;
+    for (int kz : {4, 8, 16, 32}) {
+        if (kz > p->g.n2) continue;
         set_depth(p->slots, p->g, kz);
-        launch_operator<T>(p, w, tb, w.d, w.de, w.z, w.ze, false, (T)1, nrhs, nullptr, 0, nullptr, s, false);
+        launch_operator<T>(p, w, tb, w.d, w.de, w.z, w.ze, false, (T)1, nrhs, nullptr, 0, nullptr, s, stress);
         (void)hipEventRecord(e0, s);
         for (int rep = 0; rep < 10; ++rep)
-            launch_operator<T>(p, w, tb, w.d, w.de, w.z, w.ze, false, (T)1, nrhs, nullptr, 0, nullptr, s, false);
+            launch_operator<T>(p, w, tb, w.d, w.de, w.z, w.ze, false, (T)1, nrhs, nullptr, 0, nullptr, s, stress);
         (void)hipEventRecord(e1, s);
         float ms = 0.0f;
         if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess) break;
-        if (kz == kz0) best_ms = 0.97f * ms;
-        else if (ms < best_ms) { best_ms = ms; best = kz; }
+        if (ms < best_ms) { best_ms = ms; best = kz; }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

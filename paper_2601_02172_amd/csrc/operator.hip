@@ -63,9 +63,9 @@ template <typename T> struct EdgeSet {
     T first[3][3], mid[3][3][3], last[3][3];   // [axis...][component]
 };
 
-template <int a, int b, int c, typename T, bool EB, bool ST>
+template <int a, int b, int c, typename T, bool EB>
 __device__ __forceinline__ void kuhn_tet_edges(const EdgeSet<T> &E, const T (&eb)[3][3], T lamV, T muV,
-                                               EdgeSet<T> &G, Sym<T> &S) {
+                                               EdgeSet<T> &G) {
     const T *P = E.first[a], *Q = E.mid[a][b], *R = E.last[c];
     T ea = P[a], ebb = Q[b], ec = R[c];
     T gab = Q[a] + P[b], gac = R[a] + P[c], gbc = R[b] + Q[c];
@@ -83,14 +83,6 @@ __device__ __forceinline__ void kuhn_tet_edges(const EdgeSet<T> &E, const T (&eb
     G.mid[a][b][a] = sab; G.mid[a][b][b] = sbb; G.mid[a][b][c] = sbc;
     // column c -> last edge c (shared by (a,b,c) and (b,a,c))
     G.last[c][a] += sac; G.last[c][b] += sbc; G.last[c][c] += scc;
-    if constexpr (ST) {
-        // tensor components by global axis
-        T sx[3][3];
-        sx[a][a] = saa; sx[b][b] = sbb; sx[c][c] = scc;
-        sx[a][b] = sx[b][a] = sab; sx[a][c] = sx[c][a] = sac; sx[b][c] = sx[c][b] = sbc;
-        S.xx += sx[0][0]; S.yy += sx[1][1]; S.zz += sx[2][2];
-        S.yz += sx[1][2]; S.xz += sx[0][2]; S.xy += sx[0][1];
-    }
 }
 
 template <typename T, bool EB, bool ST>
@@ -110,12 +102,24 @@ __device__ __forceinline__ void regular_voxel(const T (&U)[8][3], const T (&eb)[
                 if (a != b) E.mid[a][b][i] = U[(1 << a) | (1 << b)][i] - U[1 << a][i];
         }
     }
-    kuhn_tet_edges<0, 1, 2, T, EB, ST>(E, eb, lamV, muV, G, S);
-    kuhn_tet_edges<0, 2, 1, T, EB, ST>(E, eb, lamV, muV, G, S);
-    kuhn_tet_edges<1, 0, 2, T, EB, ST>(E, eb, lamV, muV, G, S);
-    kuhn_tet_edges<1, 2, 0, T, EB, ST>(E, eb, lamV, muV, G, S);
-    kuhn_tet_edges<2, 0, 1, T, EB, ST>(E, eb, lamV, muV, G, S);
-    kuhn_tet_edges<2, 1, 0, T, EB, ST>(E, eb, lamV, muV, G, S);
+    kuhn_tet_edges<0, 1, 2, T, EB>(E, eb, lamV, muV, G);
+    kuhn_tet_edges<0, 2, 1, T, EB>(E, eb, lamV, muV, G);
+    kuhn_tet_edges<1, 0, 2, T, EB>(E, eb, lamV, muV, G);
+    kuhn_tet_edges<1, 2, 0, T, EB>(E, eb, lamV, muV, G);
+    kuhn_tet_edges<2, 0, 1, T, EB>(E, eb, lamV, muV, G);
+    kuhn_tet_edges<2, 1, 0, T, EB>(E, eb, lamV, muV, G);
+    if constexpr (ST) {
+        // the sum of the element stresses: column a of the tensor is the sum of the
+        // forces of the four edges along axis a (every element has one of them).
+        // Taken from the finished edge forces, so that no accumulators live
+        // through the six elements
+        const auto col = [&](int i, int a) {
+            const int b = (a + 1) % 3, c = (a + 2) % 3;
+            return G.first[a][i] + G.mid[b][a][i] + G.mid[c][a][i] + G.last[a][i];
+        };
+        S.xx = col(0, 0); S.yy = col(1, 1); S.zz = col(2, 2);
+        S.yz = col(1, 2); S.xz = col(0, 2); S.xy = col(0, 1);
+    }
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         F[0][i] = -(G.first[0][i] + G.first[1][i] + G.first[2][i]);
@@ -157,15 +161,17 @@ __device__ __forceinline__ double dpp_row_shr1(double v) {
 // voxels (a - dx, b - dy): corners 0/4 from its own voxel, 1/5 from the thread
 // at tx - 1, 2/6 from ty - 1 and 3/7 from (tx - 1, ty - 1).
 // Bound in FP32: vector issue, 240 instructions a layer and wave of which the six
-// elements need 210; five waves per SIMD (six at 80 registers spill: 256x256x128
-// 117 -> 159 us).  FP64 had two workgroups a CU by LDS; with the row sums in two
-// buffers instead of three it has three (46 KB, 168 registers): one application at
-// 256x256x128 240 -> 197 us; inside a solve at 128^3 400 -> 377 us for six loads and
-// 70.4 -> 69.5 for one.  FP32 inside a solve at 128^3, six loads: 178.5 -> 168.7
-// (moduli a layer ahead, loads in the order of their use, no division in the
-// prologue).
+// elements need 210; five waves per SIMD.  Six (the LATE march below, 78
+// registers) were not faster: inside solves, six loads, 128^3 169.3 -> 172.8 us,
+// 96^3 71.4 -> 66.8, 256^3 1182 -> 1200.  FP64: latency, so three workgroups a CU
+// instead of two: 46 KB of LDS (row sums in two buffers instead of three) and at
+// most 168 registers (the stress from the finished edge forces, and one plane
+// buffer).  Inside solves: 128^3 six loads 397 -> 329 us, one load 70.4 -> 55.7;
+// 64^3 six loads 62 -> 50.4; 96^3 six loads 181 -> 150, one load 40.2 -> 31.6.
+// FP32 at 128^3, six loads: 178.5 -> 168.7 (moduli a layer ahead, loads in the
+// order of their use, no division in the prologue).
 template <typename T, bool HX, bool EB, bool ST>
-__global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regular(OpArgs<T> A) {
+__global__ __launch_bounds__(256, ST ? 3 : sizeof(T) == 4 ? 5 : 3) void k_regular(OpArgs<T> A) {
     __shared__ T Dp[3][TC * TC][3];
     __shared__ T FB[2][6][TE * TE];    // row sums for the node above, of this layer and the one before
     __shared__ double red[4 * 7];
@@ -225,8 +231,12 @@ __global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regula
     // plane kl + 3 are in flight while layer kl is computed and plane kl + 2
     // (loaded one layer earlier) is stored to LDS.  The march is unrolled by
     // three layers, so LDS slots, register buffers and exchange buffers are
-    // compile-time indices.
-    T R[3][2][3];
+    // compile-time indices.  LATE: one register buffer, whose next loads are issued
+    // when it has been stored, one layer before they are used; the 24 registers
+    // this saves are what the FP64 kernel with stress has to save for three waves
+    // per SIMD (186 registers with the ring, 24 of them spilled at 168).
+    constexpr bool LATE = ST && sizeof(T) == 8;
+    T R[LATE ? 1 : 3][2][3];
     auto fetch_plane = [&](int kk, T (&dst)[2][3]) {
         if constexpr (HX) {
             const uint32_t off = plane_off(kk);
@@ -257,9 +267,9 @@ __global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regula
 
     fetch_plane(k0 - 1, R[0]);
     store_plane(0, R[0]);
-    fetch_plane(k0, R[1]);
-    store_plane(1, R[1]);
-    if (k0 + 1 <= k1) fetch_plane(k0 + 1, R[2]);
+    fetch_plane(k0, R[LATE ? 0 : 1]);
+    store_plane(1, R[LATE ? 0 : 1]);
+    if (k0 + 1 <= k1) fetch_plane(k0 + 1, R[LATE ? 0 : 2]);
     int mv[3];                       // material / irregular index of the voxel at layers kl, kl + 1, kl + 2
     mv[0] = elem(A.vmat, colv + plane_off(k0 - 1));
     mv[1] = (k0 < k1) ? elem(A.vmat, colv + plane_off(k0)) : 0;
@@ -304,7 +314,9 @@ __global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regula
         if (m < 0) fetch_cut(m, F);
         fetch_lame(mv[st], LM[st]);
         mv[sn] = (kl + 2 < k1) ? elem(A.vmat, colv + plane_off(kl + 2)) : 0;
-        if (more2) fetch_plane(kl + 3, R[sb]);
+        if constexpr (!LATE) {
+            if (more2) fetch_plane(kl + 3, R[sb]);
+        }
         if (m >= 0) {
             T U[8][3];
 #pragma unroll
@@ -316,7 +328,7 @@ __global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regula
             }
             const T V = (T)(1.0 / 6.0);
             const T lamV = V * LM[sb][0], muV = V * LM[sb][1];
-            Sym<T> S = sym_acc_zero<T>();
+            Sym<T> S;
             regular_voxel<T, EB, ST>(U, eb, lamV, muV, F, S);
             if (ST && owner && kl >= k0) {
                 add_sym(acc7, S);
@@ -340,7 +352,10 @@ __global__ __launch_bounds__(256, ST ? 1 : sizeof(T) == 4 ? 5 : 3) void k_regula
 #pragma unroll
             for (int i = 0; i < 3; ++i) dv[i] = Dp[sb][tx + TC * ty][i];
         }
-        if (more) store_plane(sn, R[sn]);
+        if (more) store_plane(sn, R[LATE ? 0 : sn]);
+        if constexpr (LATE) {
+            if (more2) fetch_plane(kl + 3, R[0]);
+        }
         // one barrier per layer: the row sums alternate between two buffers (those
         // of layer s are read before the barrier of layer s + 1 and overwritten
         // after it), and the Dp slot written next layer was last read before this
