@@ -55,7 +55,7 @@ KERNEL_NAMES = {
     "enriched_gather": [r"k_enriched<"],
     "fft_x_forward": [r"k_fft_plane_fwd<", r"k_fft_x_fwd(_t)?<"],
     "fft_y_forward": [r"k_fft_y(_t)?<{t}(, \d+, \d+)?, false>"],
-    "fft_z_green": [r"k_fft_z_t<", r"k_fft_z_green<"],
+    "fft_z_green": [r"k_fft_z_t<", r"k_fft_z2<", r"k_fft_z_green<"],
     "fft_y_inverse": [r"k_fft_y(_t)?<{t}(, \d+, \d+)?, true>"],
     "fft_x_inverse": [r"k_fft_plane_inv<", r"k_fft_x_inv(_t)?<"],
 }
