@@ -100,7 +100,8 @@ typedef struct {
     int32_t check_every;/* host polls convergence every this many iterations (default 8; rounded up to even) */
     int32_t use_graph;  /* 1: the check_every iterations between polls are captured once into a hipGraph and
                            replayed (default 1); 0: launched one by one */
-    int32_t autotune;   /* 1: at the first solve, time the operator's tile depths and keep the fastest (default 1) */
+    int32_t autotune;   /* 1: at the first solve, time the operator's tile depths and keep the default one unless
+                           another makes an application 2 % faster (default 1) */
     void *stream;       /* hipStream_t to run on, or NULL for a library-owned stream */
     int32_t scheme;     /* XFFT_LCG (default), XFFT_NLCG, XFFT_BB or XFFT_BASIC; schemes other than
                            XFFT_LCG need precision XFFT_FP64 */

@@ -1,0 +1,186 @@
+/*
+ * Host-side runs of the library against a stand-in for the HIP runtime
+ * (tests/test_host_runtime.py builds this program, links it to libxfft.so and
+ * runs it on the CPU; no GPU is used).  The functions below take the place of
+ * the runtime's: device memory is zero-initialised host memory, kernels are
+ * counted and not run, and what the host code reads back from them (list
+ * lengths of the setup) or from the runtime (event times) is scripted.  What a
+ * scenario checks is host code only: which launches, allocations, waits and
+ * attributes the library asks for.
+ */
+#include <stdint.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include "xfft.h"
+
+typedef struct { uint32_t x, y, z; } Dim3;
+
+/* ---------------------------------------------------------------- scripted state */
+static int64_t g_totals[3];             /* irregular voxels, enriched nodes, cut elements */
+static int g_scans;                     /* scans since the last setup */
+static unsigned g_reg_grid;             /* workgroups of the last regular-voxel launch */
+static int g_last_regular;              /* the last launch was an operator application */
+static float (*g_elapsed)(void);        /* event time of the launches since the last one, < 0: the call fails */
+static int g_timings;
+
+/* ---------------------------------------------------------------- kernels */
+static struct { const void *f; char name[512]; } g_kernels[4096];
+static int g_nkernels;
+static void *g_module;
+
+void **__hipRegisterFatBinary(const void *data) { (void)data; return &g_module; }
+void __hipUnregisterFatBinary(void **m) { (void)m; }
+void __hipRegisterVar(void **m, void *var, char *hv, char *dv, int ext, size_t size, int c, int g) {
+    (void)m; (void)var; (void)hv; (void)dv; (void)ext; (void)size; (void)c; (void)g;
+}
+void __hipRegisterFunction(void **m, const void *f, char *df, const char *name, unsigned t, void *a, void *b, void *c,
+                           void *d, int *w) {
+    (void)m; (void)df; (void)t; (void)a; (void)b; (void)c; (void)d; (void)w;
+    if (g_nkernels == 4096) { fprintf(stderr, "too many kernels\n"); exit(2); }
+    g_kernels[g_nkernels].f = f;
+    snprintf(g_kernels[g_nkernels++].name, 512, "%s", name);
+}
+static const char *kernel_name(const void *f) {
+    for (int i = 0; i < g_nkernels; ++i)
+        if (g_kernels[i].f == f) return g_kernels[i].name;
+    return "";
+}
+
+static struct { Dim3 g, b; size_t lds; void *s; } g_cfg;
+int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t lds, void *s) {
+    g_cfg.g = g; g_cfg.b = b; g_cfg.lds = lds; g_cfg.s = s;
+    return 0;
+}
+int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *lds, void **s) {
+    *g = g_cfg.g; *b = g_cfg.b; *lds = g_cfg.lds; *s = g_cfg.s;
+    return 0;
+}
+int hipLaunchKernel(const void *f, Dim3 grid, Dim3 block, void **args, size_t lds, void *s) {
+    (void)block; (void)lds; (void)s;
+    const char *n = kernel_name(f);
+    g_last_regular = 0;
+    if (strstr(n, "k_regular")) { g_reg_grid = grid.x; g_last_regular = 1; }
+    if (strstr(n, "k_scan_offsets")) **(int64_t **)args[3] = g_totals[g_scans++ % 3];
+    if (strstr(n, "k_classify")) **(unsigned long long **)args[9] = (unsigned long long)g_totals[2];
+    return 0;
+}
+int hipGetLastError(void) { return 0; }
+
+/* ---------------------------------------------------------------- devices, memory, streams, events */
+int hipGetDeviceCount(int *n) { *n = 1; return 0; }
+int hipSetDevice(int d) { (void)d; return 0; }
+int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
+int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
+int hipGetSymbolAddress(void **p, const void *sym) { (void)sym; *p = calloc(1, (size_t)64 << 20); return *p ? 0 : 2; }
+int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return 0; }
+int hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
+int hipFree(void *p) { free(p); return 0; }
+int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; return hipMalloc(p, n); }
+int hipHostFree(void *p) { return hipFree(p); }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *q) { (void)k; (void)q; memcpy(d, s, n); return 0; }
+int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n); return 0; }
+int hipMemsetAsync(void *d, int v, size_t n, void *q) { (void)q; memset(d, v, n); return 0; }
+int hipStreamCreate(void **s) { return hipMalloc(s, 1); }
+int hipStreamDestroy(void *s) { return hipFree(s); }
+int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return 0; }
+int hipEventCreate(void **e) { return hipMalloc(e, 1); }
+int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return hipMalloc(e, 1); }
+int hipEventDestroy(void *e) { return hipFree(e); }
+int hipEventRecord(void *e, void *s) { (void)e; (void)s; return 0; }
+int hipEventSynchronize(void *e) { (void)e; return 0; }
+int hipEventElapsedTime(float *ms, void *a, void *b) {
+    (void)a; (void)b;
+    *ms = 1.0f;
+    if (!g_last_regular || !g_elapsed) return 0;
+    ++g_timings;
+    *ms = g_elapsed();
+    return *ms < 0.0f ? 1 : 0;
+}
+
+/* ---------------------------------------------------------------- problems */
+static int g_checks, g_fail;
+static void expect(int got, int want, const char *what) {
+    ++g_checks;
+    if (got != want) {
+        ++g_fail;
+        fprintf(stderr, "FAIL %s: got %d, want %d\n", what, got, want);
+    }
+}
+
+static xfft_problem *make_problem(int n0, int n1, int n2, int device, int precision) {
+    const int32_t n[3] = {n0, n1, n2};
+    const double len[3] = {n0, n1, n2}, lame[4] = {0.5, 0.4, 5.0, 4.0};
+    const size_t N = (size_t)n0 * n1 * n2;
+    double *L = malloc(sizeof(double) * N);
+    int32_t *ph = calloc(N, sizeof(int32_t));
+    for (size_t i = 0; i < N; ++i) L[i] = 1.0;
+    xfft_options o;
+    xfft_default_options(&o);
+    o.device = device;
+    o.precision = precision;
+    xfft_problem *p = NULL;
+    g_scans = 0;
+    expect(xfft_setup(n, len, L, ph, 2, lame, &o, &p), XFFT_OK, "setup");
+    free(L);
+    free(ph);
+    return p;
+}
+
+/* ---------------------------------------------------------------- depth of the regular-voxel march
+ * 128 x 128 x 32 has 9 x 9 tiles; the default depth is 8 planes (4 chunks).  Timings of
+ * the depths 4, 8, 16, 32 per round: t[round][depth index]. */
+enum { TILES = 81, N2 = 32 };
+static float g_t[2][4];
+static int g_fail_at, g_seen[4];
+static float depth_time(void) {
+    const int depth = N2 / (int)(g_reg_grid / TILES), c = depth == 4 ? 0 : depth == 8 ? 1 : depth == 16 ? 2 : 3;
+    if (g_timings == g_fail_at) return -1.0f;
+    const int round = g_seen[c]++ ? 1 : 0;
+    return g_t[round][c];
+}
+static int depth_of_solve(int n0, const float t[2][4], int fail_at) {
+    memcpy(g_t, t, sizeof(g_t));
+    memset(g_seen, 0, sizeof(g_seen));
+    g_timings = 0;
+    g_fail_at = fail_at;
+    const double e[6] = {1, 0, 0, 0, 0, 0};
+    double avg[6];
+    xfft_problem *p = make_problem(n0, 256 - n0, N2, 0, XFFT_FP64);
+    const int rc = xfft_solve(p, 1, e, NULL, NULL, avg, NULL, NULL);
+    expect(rc >= 0, 1, "solve");
+    xfft_destroy(p);
+    return N2 / (int)(g_reg_grid / TILES);
+}
+static void scenario_depth(const char *which) {
+    /* one case per process: results are kept per grid */
+    g_elapsed = depth_time;
+    if (!strcmp(which, "close")) {               /* 1 % ahead in both rounds: within the noise */
+        const float t[2][4] = {{1.2f, 1.0f, 0.99f, 1.1f}, {1.2f, 1.0f, 0.99f, 1.1f}};
+        expect(depth_of_solve(128, t, 0), 8, "depth 1 % faster is not taken");
+    } else if (!strcmp(which, "outlier")) {      /* the default's first timing was disturbed */
+        const float t[2][4] = {{1.2f, 1.1f, 1.02f, 1.2f}, {1.2f, 1.0f, 1.02f, 1.1f}};
+        expect(depth_of_solve(128, t, 0), 8, "a disturbed timing does not decide");
+    } else if (!strcmp(which, "faster")) {       /* and a depth that pays is taken, once per grid */
+        const float t[2][4] = {{1.2f, 1.0f, 0.96f, 0.97f}, {1.2f, 1.0f, 0.95f, 0.97f}};
+        expect(depth_of_solve(128, t, 0), 16, "depth 5 % faster is taken");
+        const float u[2][4] = {{9, 9, 9, 9}, {9, 9, 9, 9}};
+        expect(depth_of_solve(128, u, 0), 16, "depth kept for the grid");
+        expect(g_timings, 0, "no timing for a known grid");
+    } else {                                     /* a failed timing: default, and nothing kept */
+        const float t[2][4] = {{0.5f, 1.0f, 0.9f, 1.2f}, {0.5f, 1.0f, 0.9f, 1.2f}};
+        expect(depth_of_solve(128, t, 3), 8, "default depth after a failed timing");
+        const float u[2][4] = {{1.2f, 1.0f, 0.9f, 1.2f}, {1.2f, 1.0f, 0.9f, 1.2f}};
+        expect(depth_of_solve(128, u, 0), 16, "timed again by the next problem");
+    }
+}
+
+int main(int argc, char **argv) {
+    if (argc == 3 && !strcmp(argv[1], "depth")) scenario_depth(argv[2]);
+    else return 2;
+    if (g_fail) return 1;
+    printf("host_runtime: %d checks passed\n", g_checks);
+    return 0;
+}
