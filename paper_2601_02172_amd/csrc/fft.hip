@@ -1290,10 +1290,6 @@ int green_slots(const Geometry &g) {
     return m;
 }
 
-template <typename K> static void allow_lds(K kernel, size_t bytes) {
-    if (bytes > 65536) (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-}
-
 // one workgroup per (load, component, z plane); two are resident per CU
 static unsigned plane_grid(const xfft_problem *p, int nrhs) { return (unsigned)(3 * p->g.n2 * nrhs); }
 
@@ -1301,16 +1297,16 @@ template <typename T, int N>
 static void plane_fwd(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, const cpx<T> *tw, T *f,
                       const T *z, cpx<T> *spec) {
     const size_t lds = (size_t)PlaneCfg<N>::ELEMS * sizeof(cpx<T>);
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_plane_fwd<T, N>, lds); init = true; }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, p->device, k_fft_plane_fwd<T, N>, lds);
     k_fft_plane_fwd<T, N><<<plane_grid(p, nrhs), PlaneCfg<N>::NT, lds, s>>>(A, tw, f, z, spec, nrhs);
 }
 template <typename T, int N>
 static void plane_inv(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, const cpx<T> *tw,
                       const cpx<T> *spec, int mode, T *out, T *u, T *d, const EnrFin<T> &E) {
     const size_t lds = (size_t)PlaneCfg<N>::ELEMS * sizeof(cpx<T>);
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_plane_inv<T, N>, lds); init = true; }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, p->device, k_fft_plane_inv<T, N>, lds);
     k_fft_plane_inv<T, N><<<plane_grid(p, nrhs), PlaneCfg<N>::NT, lds, s>>>(A, tw, spec, mode, out, u, d, nrhs, E);
 }
 template <typename T, int N2, int TK>
@@ -1321,15 +1317,15 @@ static void zpass_tk(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, 
     // workgroups of k_fft_z_t share a CU (64 registers, eight waves per SIMD)
     const int nh = p->g.nh, ntiles = (nh + TK - 1) / TK, tk = (nh + ntiles - 1) / ntiles;
     const int64_t grid = ((int64_t)p->g.n1 * ntiles + E.nblk) * nrhs;
-    static bool init = false;
+    static std::atomic<uint64_t> lds_ok{0};
     if constexpr (zp_two<T>(N2)) {
         const size_t line = Z2Cfg<T, N2, TK>::LS * sizeof(cpx<T>);
-        if (!init) { allow_lds(k_fft_z2<T, N2, TK>, (size_t)3 * TK * line); init = true; }
+        allow_lds(lds_ok, p->device, k_fft_z2<T, N2, TK>, (size_t)3 * TK * line);
         k_fft_z2<T, N2, TK><<<(unsigned)grid, Z2Cfg<T, N2, TK>::NT, (size_t)3 * tk * line, s>>>(
             A, tb.tw[2], tb.half[0], tb.half[1], tb.half[2], spec, sz, sy, nrhs, E);
     } else {
         const size_t line = (size_t)lds_ls<3 * TK >= 32>(N2) * sizeof(cpx<T>);
-        if (!init) { allow_lds(k_fft_z_t<T, N2, TK>, (size_t)3 * TK * line); init = true; }
+        allow_lds(lds_ok, p->device, k_fft_z_t<T, N2, TK>, (size_t)3 * TK * line);
         k_fft_z_t<T, N2, TK><<<(unsigned)grid, 512, (size_t)3 * tk * line, s>>>(
             A, tb.tws[2], tb.half[0], tb.half[1], tb.half[2], spec, sz, sy, nrhs, E);
     }
@@ -1347,8 +1343,8 @@ static void zpass(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s, con
 template <typename T, int N> static void xfwd_t(const xfft_problem *p, FftArgs A, int nrhs, hipStream_t s,
                                                 const cpx<T> *tw, T *f, const T *z, cpx<T> *spec) {
     const size_t lds = (size_t)XCfg<T, N>::PP * XCfg<T, N>::LS * sizeof(cpx<T>);
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_x_fwd_t<T, N>, lds); init = true; }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, p->device, k_fft_x_fwd_t<T, N>, lds);
     const int64_t npairs = (int64_t)3 * p->g.n2 * p->g.n1 / 2;
     const int64_t nblk = (npairs + XCfg<T, N>::PP - 1) / XCfg<T, N>::PP;
     k_fft_x_fwd_t<T, N><<<(unsigned)(nblk * nrhs), 256, lds, s>>>(A, tw, f, z, spec, nrhs);
@@ -1357,8 +1353,8 @@ template <typename T, int N> static void xinv_t(const xfft_problem *p, FftArgs A
                                                 const cpx<T> *tw, const cpx<T> *spec, int mode, T *out, T *u,
                                                 T *d, const EnrFin<T> &E) {
     const size_t lds = (size_t)XCfg<T, N>::PP * XCfg<T, N>::LS * sizeof(cpx<T>);
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_x_inv_t<T, N>, lds); init = true; }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, p->device, k_fft_x_inv_t<T, N>, lds);
     const int64_t npairs = (int64_t)3 * p->g.n2 * p->g.n1 / 2;
     const int64_t nblk = (npairs + XCfg<T, N>::PP - 1) / XCfg<T, N>::PP;
     // four enriched nodes per thread
@@ -1370,8 +1366,8 @@ template <typename T, int N1, bool INV> static void ypass_t(const xfft_problem *
     // about 2048 elements per workgroup
     constexpr int TK = N1 >= 256 ? 8 : N1 >= 96 ? 16 : N1 >= 36 ? 32 : 64;
     const size_t lds = (size_t)TK * lds_ls<TK >= 32 && (N1 & (N1 - 1)) != 0>(N1) * sizeof(cpx<T>);
-    static bool init = false;
-    if (!init) { allow_lds(k_fft_y_t<T, N1, TK, INV>, lds); init = true; }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, p->device, k_fft_y_t<T, N1, TK, INV>, lds);
     const int ntiles = (p->g.nh + TK - 1) / TK;
     const int64_t nblk = (int64_t)3 * p->g.n2 * ntiles;
     k_fft_y_t<T, N1, TK, INV><<<(unsigned)(nblk * nrhs), 256, lds, s>>>(A, tw, spec, nrhs);

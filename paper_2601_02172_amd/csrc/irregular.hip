@@ -534,14 +534,10 @@ IrrArgs<T> irr_args(const xfft_problem *p, const Tables<T> &tb) {
 }
 
 template <typename T, bool HX, bool EB, bool ST>
-void launch_irr(const IrrArgs<T> &A, int nrhs, hipStream_t s) {
+void launch_irr(int device, const IrrArgs<T> &A, int nrhs, hipStream_t s) {
     const size_t lds = sizeof(IrrShared<T>);
-    static bool init = false;
-    if (!init && lds > 65536) {
-        (void)hipFuncSetAttribute((const void *)k_irregular<T, HX, EB, ST>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        init = true;
-    }
+    static std::atomic<uint64_t> lds_ok{0};
+    allow_lds(lds_ok, device, k_irregular<T, HX, EB, ST>, lds);
     k_irregular<T, HX, EB, ST><<<(unsigned)(A.blocks * nrhs), BT, lds, s>>>(A);
 }
 
@@ -556,11 +552,11 @@ void launch_irregular(xfft_problem *p, const Tables<T> &tb, const T *x, const T 
     A.partial = partial; A.nslots = p->nslots; A.slot0 = p->slots.cut0; A.vstress = vstress;
     const bool hx = x != nullptr;
     xfft_prof_mark(p, -1, s);
-    if (hx && use_ebar) launch_irr<T, true, true, true>(A, nrhs, s);
-    else if (hx && stress) launch_irr<T, true, false, true>(A, nrhs, s);
-    else if (hx) launch_irr<T, true, false, false>(A, nrhs, s);
-    else if (use_ebar) launch_irr<T, false, true, true>(A, nrhs, s);
-    else launch_irr<T, false, false, false>(A, nrhs, s);
+    if (hx && use_ebar) launch_irr<T, true, true, true>(p->device, A, nrhs, s);
+    else if (hx && stress) launch_irr<T, true, false, true>(p->device, A, nrhs, s);
+    else if (hx) launch_irr<T, true, false, false>(p->device, A, nrhs, s);
+    else if (use_ebar) launch_irr<T, false, true, true>(p->device, A, nrhs, s);
+    else launch_irr<T, false, false, false>(p->device, A, nrhs, s);
     xfft_prof_mark(p, K_IRREGULAR + (sizeof(T) == 8 ? K_COUNT : 0), s);
 }
 

@@ -1,9 +1,21 @@
 // Kernel launchers of the X-FFT GPU library (internal).
 #pragma once
 
+#include <atomic>
+
 #include "common.h"
 
 namespace xfft {
+
+// Allows a kernel more dynamic LDS than the 64 KB that every launch may take.  The
+// attribute belongs to the kernel on one device, so each launch site remembers the
+// devices (bit per device, below 64 as setup requires) that have it.
+template <typename K> inline void allow_lds(std::atomic<uint64_t> &done, int device, K kernel, size_t bytes) {
+    const uint64_t bit = (uint64_t)1 << device;
+    if (bytes <= 65536 || (done.load(std::memory_order_acquire) & bit)) return;
+    if (hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess)
+        done.fetch_or(bit, std::memory_order_release);
+}
 
 SlotLayout slot_layout(const Geometry &g);
 // regular-voxel operator depth (planes per block); kz in {4, 8, 16}

@@ -24,9 +24,10 @@ static unsigned g_reg_grid;             /* workgroups of the last regular-voxel 
 static int g_last_regular;              /* the last launch was an operator application */
 static float (*g_elapsed)(void);        /* event time of the launches since the last one, < 0: the call fails */
 static int g_timings;
+static int g_device, g_big_launches, g_bad_launches;   /* current device; launches above 64 KB of dynamic LDS */
 
 /* ---------------------------------------------------------------- kernels */
-static struct { const void *f; char name[512]; } g_kernels[4096];
+static struct { const void *f; char name[512]; size_t lds[2]; } g_kernels[4096];
 static int g_nkernels;
 static void *g_module;
 
@@ -42,10 +43,11 @@ void __hipRegisterFunction(void **m, const void *f, char *df, const char *name, 
     g_kernels[g_nkernels].f = f;
     snprintf(g_kernels[g_nkernels++].name, 512, "%s", name);
 }
-static const char *kernel_name(const void *f) {
+static int kernel_index(const void *f) {
     for (int i = 0; i < g_nkernels; ++i)
-        if (g_kernels[i].f == f) return g_kernels[i].name;
-    return "";
+        if (g_kernels[i].f == f) return i;
+    fprintf(stderr, "kernel not registered\n");
+    exit(2);
 }
 
 static struct { Dim3 g, b; size_t lds; void *s; } g_cfg;
@@ -58,8 +60,15 @@ int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *lds, void **s) {
     return 0;
 }
 int hipLaunchKernel(const void *f, Dim3 grid, Dim3 block, void **args, size_t lds, void *s) {
-    (void)block; (void)lds; (void)s;
-    const char *n = kernel_name(f);
+    (void)block; (void)s;
+    const int k = kernel_index(f);
+    const char *n = g_kernels[k].name;
+    if (lds > 65536) {
+        ++g_big_launches;
+        if (g_kernels[k].lds[g_device] < lds) {
+            if (!g_bad_launches++) fprintf(stderr, "%s: %zu bytes of LDS on device %d\n", n, lds, g_device);
+        }
+    }
     g_last_regular = 0;
     if (strstr(n, "k_regular")) { g_reg_grid = grid.x; g_last_regular = 1; }
     if (strstr(n, "k_scan_offsets")) **(int64_t **)args[3] = g_totals[g_scans++ % 3];
@@ -69,10 +78,10 @@ int hipLaunchKernel(const void *f, Dim3 grid, Dim3 block, void **args, size_t ld
 int hipGetLastError(void) { return 0; }
 
 /* ---------------------------------------------------------------- devices, memory, streams, events */
-int hipGetDeviceCount(int *n) { *n = 1; return 0; }
-int hipSetDevice(int d) { (void)d; return 0; }
+int hipGetDeviceCount(int *n) { *n = 2; return 0; }
+int hipSetDevice(int d) { g_device = d; return 0; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return 0; }
-int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return 0; }
+int hipFuncSetAttribute(const void *f, int a, int v) { (void)a; g_kernels[kernel_index(f)].lds[g_device] = (size_t)v; return 0; }
 int hipGetSymbolAddress(void **p, const void *sym) { (void)sym; *p = calloc(1, (size_t)64 << 20); return *p ? 0 : 2; }
 int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return 0; }
 int hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
@@ -177,8 +186,35 @@ static void scenario_depth(const char *which) {
     }
 }
 
+/* ---------------------------------------------------------------- dynamic LDS on a second device
+ * Every launch above 64 KB needs the kernel's attribute on the device it runs on. */
+static void scenario_devices(int n, int precision) {
+    g_totals[0] = 100; g_totals[1] = 300; g_totals[2] = 400;
+    for (int dev = 0; dev < 2; ++dev) {
+        xfft_problem *p = make_problem(n, n, 16, dev, precision);
+        const size_t ndof = 3 * ((size_t)n * n * 16 + 300);
+        double *x = calloc(ndof, sizeof(double)), *y = calloc(ndof, sizeof(double)), avg[36], res2;
+        double e[36] = {0};
+        for (int k = 0; k < 6; ++k) e[7 * k] = 1.0;
+        const int before = g_big_launches;
+        expect(xfft_apply_operator_noalloc(p, x, e, y, avg, NULL), XFFT_OK, "noalloc operator");
+        expect(xfft_apply_operator_noalloc(p, x, NULL, y, NULL, NULL), XFFT_OK, "noalloc operator");
+        for (int prec = XFFT_FP64; prec <= XFFT_FP32; prec += 2) {
+            expect(xfft_apply_operator(p, prec, x, e, y, avg), XFFT_OK, "operator");
+            expect(xfft_apply_precond(p, prec, x, y, &res2), XFFT_OK, "preconditioner");
+        }
+        expect(xfft_solve(p, 6, e, NULL, NULL, avg, NULL, NULL) >= 0, 1, "solve");
+        expect(g_big_launches > before, 1, "launches above 64 KB");
+        expect(g_bad_launches, 0, "launches without the attribute on their device");
+        free(x);
+        free(y);
+        xfft_destroy(p);
+    }
+}
+
 int main(int argc, char **argv) {
-    if (argc == 3 && !strcmp(argv[1], "depth")) scenario_depth(argv[2]);
+    if (argc == 4 && !strcmp(argv[1], "devices")) scenario_devices(atoi(argv[2]), atoi(argv[3]));
+    else if (argc == 3 && !strcmp(argv[1], "depth")) scenario_depth(argv[2]);
     else return 2;
     if (g_fail) return 1;
     printf("host_runtime: %d checks passed\n", g_checks);

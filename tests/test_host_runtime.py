@@ -7,7 +7,9 @@ code asks for can be counted and the event times of the autotuner scripted:
 * depth of the regular-voxel march: a depth that is ahead by less than the noise
   of the timings does not replace the default, nor does one disturbed timing
   decide; a depth that pays is taken and kept for the grid; after a failed
-  timing the default stays and the next problem times again.
+  timing the default stays and the next problem times again;
+* dynamic LDS: on each of two devices of one process, every launch with more
+  than 64 KB follows the attribute that allows it on that device.
 """
 
 import os
@@ -44,3 +46,8 @@ def _run(exe, *args):
 @pytest.mark.parametrize("case", ["close", "outlier", "faster", "failed"])
 def test_depth_of_the_regular_march(program, case):
     _run(program, "depth", case)
+
+
+@pytest.mark.parametrize("n,precision", [(128, 0), (96, 1), (108, 0)])
+def test_lds_attribute_on_every_device(program, n, precision):
+    _run(program, "devices", str(n), str(precision))
