@@ -852,22 +852,10 @@ void xfft_destroy(xfft_problem *p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     if (p->stream) (void)hipStreamSynchronize(p->stream);
-    void *ptrs[] = {p->Ls, p->phase, p->vmat, p->irr, p->irr_j, p->irr_lab, p->jlist, p->enr_src, p->d0, p->partial,
-                    p->scal, p->flags, p->ebar, p->sum7, p->sol_u, p->sol_ue, p->t64.lame, p->t64.d0is, p->t64.irr_L,
-                    p->t32.lame, p->t32.d0is, p->t32.irr_L, p->t64.cut_M, p->t32.cut_M, p->irr_node,
-                    p->tet_cut, p->tet_uncut, p->cut_pos, p->blk_cut, p->cut_lab, p->uncut_lab};
+    void *ptrs[] = {p->Ls, p->phase, p->vmat, p->geom_block, p->table_block, p->partial, p->scal, p->flags, p->ebar,
+                    p->sum7, p->sol_u, p->sol_ue};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
-    for (int a = 0; a < 3; ++a) {
-        if (p->t64.tw[a]) (void)hipFree(p->t64.tw[a]);
-        if (p->t64.tws[a]) (void)hipFree(p->t64.tws[a]);
-        if (p->t32.tws[a]) (void)hipFree(p->t32.tws[a]);
-        if (p->t32.tw[a]) (void)hipFree(p->t32.tw[a]);
-        if (p->t64.half[a]) (void)hipFree(p->t64.half[a]);
-        if (p->t32.half[a]) (void)hipFree(p->t32.half[a]);
-    }
-    if (p->t64.twp) (void)hipFree(p->t64.twp);
-    if (p->t32.twp) (void)hipFree(p->t32.twp);
     drop_graph(p);
     free_voxel_matrices(p);
     free_work(p->w64);

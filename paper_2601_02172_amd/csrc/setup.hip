@@ -192,19 +192,23 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_emit(int64_t n, const uint8_t *
     }
 }
 
+// labels of element t of an irregular voxel; returns whether it is cut
 template <int t>
-__device__ __forceinline__ void irr_labels_tet(const double (&Lc)[8], const int (&pc)[8], int32_t *out,
+__device__ __forceinline__ bool irr_labels_tet(const double (&Lc)[8], const int (&pc)[8], int32_t *out,
                                                int64_t stride) {
     bool cut, ml;
     int lu, lp, ln;
     classify_tet<t>(Lc, pc, cut, lu, lp, ln, ml);
     out[(2 * t) * stride] = cut ? lp : lu;
     out[(2 * t + 1) * stride] = cut ? ln : lu;
+    return cut;
 }
 
+// corner tables and element labels of the irregular voxels and, per element
+// 6 q + t, whether it is cut
 __global__ void k_irr_tables(int64_t nirr, int n0, int n1, int n2, const int32_t *irr, const double *Ls,
-                             const int32_t *phase, const int32_t *jmap, int32_t *irr_j, int32_t *irr_lab,
-                             double *irr_L64, float *irr_L32) {
+                             const int32_t *phase, const int32_t *jmap, int32_t *irr_j, int32_t *irr_node,
+                             int32_t *irr_lab, double *irr_L64, float *irr_L32, uint8_t *cut) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nirr) return;
     const int64_t v = irr[q];
@@ -217,41 +221,18 @@ __global__ void k_irr_tables(int64_t nirr, int n0, int n1, int n2, const int32_t
         Lc[c] = Ls[nd];
         pc[c] = phase[nd];
         irr_j[c * nirr + q] = jmap[nd];
+        irr_node[c * nirr + q] = (int32_t)nd;
         irr_L64[c * nirr + q] = Lc[c];
         irr_L32[c * nirr + q] = (float)Lc[c];
     }
     int32_t *lab = irr_lab + q;
-    irr_labels_tet<0>(Lc, pc, lab, nirr);
-    irr_labels_tet<1>(Lc, pc, lab, nirr);
-    irr_labels_tet<2>(Lc, pc, lab, nirr);
-    irr_labels_tet<3>(Lc, pc, lab, nirr);
-    irr_labels_tet<4>(Lc, pc, lab, nirr);
-    irr_labels_tet<5>(Lc, pc, lab, nirr);
-}
-
-// node of every corner and, per element 6 q + t, whether it is cut
-__global__ void k_tet_flags(int64_t nirr, int n0, int n1, int n2, const int32_t *irr, const double *irr_L64,
-                            int32_t *irr_node, uint8_t *cut) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= nirr) return;
-    const int64_t v = irr[q];
-    const int i = (int)(v % n0), j = (int)((v / n0) % n1), k = (int)(v / ((int64_t)n0 * n1));
-    double Lc[8];
-#pragma unroll
-    for (int c = 0; c < 8; ++c) {
-        Lc[c] = irr_L64[c * nirr + q];
-        irr_node[c * nirr + q] = (int32_t)corner_node(i, j, k, c, n0, n1, n2);
-    }
-#pragma unroll
-    for (int t = 0; t < 6; ++t) {
-        bool anyp = false, anyn = false;
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            anyp |= Lc[tet_corner(t, a)] > 0.0;
-            anyn |= Lc[tet_corner(t, a)] < 0.0;
-        }
-        cut[6 * q + t] = anyp && anyn ? 1 : 0;
-    }
+    uint8_t *ct = cut + 6 * q;
+    ct[0] = irr_labels_tet<0>(Lc, pc, lab, nirr);
+    ct[1] = irr_labels_tet<1>(Lc, pc, lab, nirr);
+    ct[2] = irr_labels_tet<2>(Lc, pc, lab, nirr);
+    ct[3] = irr_labels_tet<3>(Lc, pc, lab, nirr);
+    ct[4] = irr_labels_tet<4>(Lc, pc, lab, nirr);
+    ct[5] = irr_labels_tet<5>(Lc, pc, lab, nirr);
 }
 
 // first cut element of every run of IRR_VB irregular voxels (lower bound of 6 q0 in the ascending list)
@@ -416,30 +397,39 @@ __global__ void k_enr_src(int64_t nX, int n0, int n1, int n2, const int32_t *jli
     }
 }
 
-__global__ void k_fft_tables(int n, double2 *tw64, float2 *tw32, double *half64, float *half32) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
+__device__ __forceinline__ double2 twiddle(int t, int n) {
     double s, c;
     sincospi(-2.0 * (double)t / (double)n, &s, &c);
-    tw64[t] = make_double2(c, s);
-    tw32[t] = make_float2((float)c, (float)s);
+    return make_double2(c, s);
+}
+
+// Twiddles exp(-2 pi i t / n), half-angle tables, and the twiddles in the stage
+// order of the compile-time plans: st* for the plan of the line passes, pl* (null:
+// none) for the plan of the xy-plane kernels, which is the narrow one in FP64.
+__global__ void k_fft_tables(int n, double2 *tw64, float2 *tw32, double *half64, float *half32, double2 *st64,
+                             float2 *st32, double2 *pl64, float2 *pl32) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    const auto narrow = [](double2 w) { return make_float2((float)w.x, (float)w.y); };
+    const double2 w = twiddle(t, n);
+    tw64[t] = w;
+    tw32[t] = narrow(w);
     double hs, hc;
     sincospi((double)t / (double)n, &hs, &hc);
     half64[2 * t] = hs;
     half64[2 * t + 1] = hc;
     half32[2 * t] = (float)hs;
     half32[2 * t + 1] = (float)hc;
-}
-
-// stage-major twiddle tables (gathered from the natural-order ones, so the
-// values are identical)
-__global__ void k_fft_stage_tables(int n, const double2 *tw64, const float2 *tw32, double2 *st64, float2 *st32,
-                                   bool narrow64) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n) return;
-    const int t = e < n - 1 ? fft_stage_index(n, e) : -1, t64 = narrow64 && e < n - 1 ? fft_stage_index(n, e, true) : t;
-    st64[e] = t64 >= 0 ? tw64[t64] : make_double2(1.0, 0.0);
-    st32[e] = t >= 0 ? tw32[t] : make_float2(1.0f, 0.0f);
+    // entry t of the stage order; 1 where a length has no compile-time plan
+    const int i = t < n - 1 ? fft_stage_index(n, t) : -1;
+    const double2 ws = i >= 0 ? twiddle(i, n) : make_double2(1.0, 0.0);
+    st64[t] = ws;
+    st32[t] = narrow(ws);
+    if (pl64) {
+        const int ip = t < n - 1 ? fft_stage_index(n, t, true) : -1;
+        pl64[t] = ip >= 0 ? twiddle(ip, n) : make_double2(1.0, 0.0);
+        pl32[t] = narrow(ws);
+    }
 }
 
 __global__ void k_lame(int n, const double *lame, float *lame32) {
@@ -456,193 +446,190 @@ constexpr int XFFT_EDEVICE_INTERNAL = -3;
 constexpr int XFFT_ENOMEM_INTERNAL = -2;
 constexpr int XFFT_EINVAL_INTERNAL = -1;
 
-int compact(hipStream_t s, int64_t n, const uint8_t *flag, int32_t *map, const int32_t *lab, int32_t **list_out,
-            int64_t *count_out, int32_t **comp_out = nullptr) {
-    const int nb = (int)((n + SCAN_CH - 1) / SCAN_CH);
-    int32_t *cnt = nullptr, *off = nullptr;
-    int64_t *tot = nullptr;
-    if (hipMalloc(&cnt, sizeof(int32_t) * nb) != hipSuccess) return XFFT_ENOMEM_INTERNAL;
-    if (hipMalloc(&off, sizeof(int32_t) * nb) != hipSuccess) { (void)hipFree(cnt); return XFFT_ENOMEM_INTERNAL; }
-    if (hipMalloc(&tot, sizeof(int64_t)) != hipSuccess) { (void)hipFree(cnt); (void)hipFree(off); return XFFT_ENOMEM_INTERNAL; }
+int scan_blocks(int64_t n) { return (int)((n + SCAN_CH - 1) / SCAN_CH); }
+
+// Ordered compaction of n flags in two halves, so that the host waits once for all
+// list lengths it needs: scan leaves the block offsets in off and the length in
+// total, emit writes the lists.
+void scan_flags(hipStream_t s, int64_t n, const uint8_t *flag, int32_t *cnt, int32_t *off, int64_t *total) {
+    const int nb = scan_blocks(n);
     k_scan_count<<<nb, SCAN_T, 0, s>>>(n, flag, cnt);
-    k_scan_offsets<<<1, 1024, 0, s>>>(nb, cnt, off, tot);
-    int64_t total = 0;
-    int rc = 0;
-    if (hipMemcpyAsync(&total, tot, sizeof(int64_t), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        rc = XFFT_EDEVICE_INTERNAL;
-    int32_t *list = nullptr;
-    if (!rc && hipMalloc(&list, sizeof(int32_t) * (total > 0 ? total : 1)) != hipSuccess) rc = XFFT_ENOMEM_INTERNAL;
-    int32_t *comp = nullptr;
-    if (!rc && comp_out && hipMalloc(&comp, sizeof(int32_t) * (n > total ? n - total : 1)) != hipSuccess)
-        rc = XFFT_ENOMEM_INTERNAL;
-    if (!rc) k_scan_emit<<<nb, SCAN_T, 0, s>>>(n, flag, off, list, map, lab, comp);
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = XFFT_EDEVICE_INTERNAL;
-    (void)hipFree(cnt);
-    (void)hipFree(off);
-    (void)hipFree(tot);
-    if (rc) { if (list) (void)hipFree(list); if (comp) (void)hipFree(comp); return rc; }
-    *list_out = list;
-    if (comp_out) *comp_out = comp;
-    *count_out = total;
-    return 0;
+    k_scan_offsets<<<1, 1024, 0, s>>>(nb, cnt, off, total);
 }
+void emit_lists(hipStream_t s, int64_t n, const uint8_t *flag, const int32_t *off, int32_t *list, int32_t *map,
+                const int32_t *lab, int32_t *comp) {
+    k_scan_emit<<<scan_blocks(n), SCAN_T, 0, s>>>(n, flag, off, list, map, lab, comp);
+}
+
+// Parts of one allocation, each on a 256-byte boundary: laid out without a base
+// first, for the size, then with it.
+struct Carve {
+    unsigned char *base = nullptr;
+    size_t size = 0;
+    template <typename P> void take(P *&ptr, int64_t count) {
+        if (base) ptr = reinterpret_cast<P *>(base + size);
+        size += (sizeof(P) * (size_t)count + 255) & ~(size_t)255;
+    }
+};
+template <typename F> bool carve(void **block, F parts) {
+    Carve c;
+    parts(c);
+    if (hipMalloc(block, c.size ? c.size : 1) != hipSuccess) return false;
+    c.base = static_cast<unsigned char *>(*block);
+    c.size = 0;
+    parts(c);
+    return true;
+}
+
+// what the host reads back from a setup, in the order of the kernels that fill it
+struct SetupCounts {
+    unsigned long long elements[2];   // cut elements, of these with several labels on a side
+    int64_t irregular, enriched, cut; // list lengths
+    int err, pad;
+};
 
 }  // namespace
 
-// Lists of the cut and uncut elements of the irregular voxels and their tables.
-static int element_lists(xfft_problem *p) {
-    hipStream_t s = p->stream;
-    const Geometry &g = p->g;
-    const int64_t ne = 6 * g.nirr;
-    uint8_t *cut = nullptr;
-    int64_t nc = 0;
-    int rc = 0;
-    if (hipMalloc(&cut, ne) != hipSuccess || hipMalloc(&p->cut_pos, sizeof(int32_t) * ne) != hipSuccess)
-        rc = XFFT_ENOMEM_INTERNAL;
-    if (!rc) {
-        k_tet_flags<<<(unsigned)((g.nirr + 255) / 256), 256, 0, s>>>(g.nirr, g.n0, g.n1, g.n2, p->irr, p->t64.irr_L,
-                                                                     p->irr_node, cut);
-        rc = compact(s, ne, cut, p->cut_pos, nullptr, &p->tet_cut, &nc, &p->tet_uncut);
-    }
-    const int64_t nu = ne - nc;
-    const int nblk = (int)((g.nirr + IRR_VB - 1) / IRR_VB);
-    const size_t mc = nc > 0 ? nc : 1, mu = nu > 0 ? nu : 1;
-    if (!rc && (nc != p->n_cut_elements || hipMalloc(&p->blk_cut, sizeof(int32_t) * (nblk + 1)) != hipSuccess ||
-                hipMalloc(&p->t64.cut_M, sizeof(double) * 10 * mc) != hipSuccess ||
-                hipMalloc(&p->t32.cut_M, sizeof(float) * 10 * mc) != hipSuccess ||
-                hipMalloc(&p->cut_lab, sizeof(int32_t) * 2 * mc) != hipSuccess ||
-                hipMalloc(&p->uncut_lab, sizeof(int32_t) * mu) != hipSuccess))
-        rc = nc != p->n_cut_elements ? XFFT_EDEVICE_INTERNAL : XFFT_ENOMEM_INTERNAL;
-    if (!rc) {
-        k_blk_cut<<<(unsigned)((nblk + 256) / 256), 256, 0, s>>>(nblk, nc, p->tet_cut, p->blk_cut);
-        if (nc)
-            k_cut_moments<<<(unsigned)((nc + 255) / 256), 256, 0, s>>>(nc, g.nirr, p->tet_cut, p->t64.irr_L,
-                                                                       p->irr_lab, p->t64.cut_M, p->t32.cut_M,
-                                                                       p->cut_lab);
-        if (nu)
-            k_uncut_lab<<<(unsigned)((nu + 255) / 256), 256, 0, s>>>(nu, g.nirr, p->tet_uncut, p->irr_lab,
-                                                                     p->uncut_lab);
-    }
-    if (cut) (void)hipFree(cut);
-    return rc;
-}
-
 // L_dev_raw: device copy of the caller's level set (units of len).
+//
+// A small grid pays for the calls of its setup and not for the kernels: with 62
+// allocations, 17 frees and 10 waits 16^3 took 440 us to build, 64^3 725 us and
+// 128^3 2.4 ms; with 8, 2 and 3 they take 290 us, 570 us and 2.1 ms.  So the
+// scratch, the geometry tables and the FFT tables are one allocation each, and
+// the host waits for the list lengths once and for the end once.
 int run_setup(xfft_problem *p, const double *L_dev_raw) {
     hipStream_t s = p->stream;
     Geometry &g = p->g;
     const int64_t N = g.N;
     const int tb = 256;
-    const unsigned nbN = (unsigned)((N + tb - 1) / tb);
-    int *err = nullptr;
-    unsigned long long *counts = nullptr;
-    uint8_t *vflag = nullptr, *jflag = nullptr;
-    int32_t *vlab = nullptr, *jmap = nullptr;
-    int rc = 0;
-    auto cleanup = [&]() {
-        if (err) (void)hipFree(err);
-        if (counts) (void)hipFree(counts);
-        if (vflag) (void)hipFree(vflag);
-        if (jflag) (void)hipFree(jflag);
-        if (vlab) (void)hipFree(vlab);
-        if (jmap) (void)hipFree(jmap);
+    const auto blocks = [&](int64_t n) { return (unsigned)((n + tb - 1) / tb); };
+    // the flags of the elements (6 bytes a voxel, at most) take the place of the
+    // flags and labels of voxels and nodes, which are read for the last time before
+    SetupCounts *cnt = nullptr;
+    uint8_t *jflag = nullptr, *vflag = nullptr;
+    int32_t *vlab = nullptr, *jmap = nullptr, *sc[3] = {}, *so[3] = {};
+    const int64_t scan_n[3] = {N, N, 6 * N};
+    void *scratch = nullptr;
+    const auto parts = [&](Carve &c) {
+        c.take(cnt, 1);
+        c.take(jflag, 6 * N);
+        c.take(jmap, N);
+        for (int q = 0; q < 3; ++q) {
+            c.take(sc[q], scan_blocks(scan_n[q]));
+            c.take(so[q], scan_blocks(scan_n[q]));
+        }
     };
-    if (hipMalloc(&err, sizeof(int)) != hipSuccess || hipMalloc(&counts, 2 * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc(&vflag, N) != hipSuccess || hipMalloc(&jflag, N) != hipSuccess ||
-        hipMalloc(&vlab, 4 * N) != hipSuccess || hipMalloc(&jmap, 4 * N) != hipSuccess) {
-        cleanup();
-        return XFFT_ENOMEM_INTERNAL;
-    }
-    if (hipMemsetAsync(err, 0, sizeof(int), s) != hipSuccess ||
-        hipMemsetAsync(counts, 0, 2 * sizeof(unsigned long long), s) != hipSuccess ||
-        hipMemsetAsync(jflag, 0, N, s) != hipSuccess) {
-        cleanup();
-        return XFFT_EDEVICE_INTERNAL;
-    }
-    k_snap<<<nbN, tb, 0, s>>>(N, L_dev_raw, 1.0 / p->h, p->snap_eps, p->phase, g.nphase, p->Ls, err);
-    int herr = 0;
-    if (hipMemcpyAsync(&herr, err, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess) {
-        cleanup();
-        return XFFT_EDEVICE_INTERNAL;
-    }
-    if (herr) {
-        cleanup();
-        return XFFT_EINVAL_INTERNAL;
-    }
-    k_classify<<<nbN, tb, 0, s>>>(g.n0, g.n1, g.n2, p->Ls, p->phase, p->p1, vflag, vlab, jflag, counts);
-    rc = compact(s, N, vflag, p->vmat, vlab, &p->irr, &g.nirr);
-    if (!rc) rc = compact(s, N, jflag, jmap, nullptr, &p->jlist, &g.nX);
-    unsigned long long hc[2] = {0, 0};
-    if (!rc && (hipMemcpyAsync(hc, counts, sizeof(hc), hipMemcpyDeviceToHost, s) != hipSuccess ||
-                hipStreamSynchronize(s) != hipSuccess))
+    if (!carve(&scratch, parts)) return XFFT_ENOMEM_INTERNAL;
+    vflag = jflag + N;
+    vlab = reinterpret_cast<int32_t *>(jflag + 2 * N);      // N is a multiple of 8
+    uint8_t *cut = jflag;
+    int rc = 0;
+    SetupCounts h;
+    const auto fetch = [&]() {
+        if (hipMemcpyAsync(&h, cnt, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess ||
+            hipStreamSynchronize(s) != hipSuccess)
+            rc = XFFT_EDEVICE_INTERNAL;
+    };
+    if (hipMemsetAsync(cnt, 0, sizeof(SetupCounts), s) != hipSuccess || hipMemsetAsync(jflag, 0, N, s) != hipSuccess)
         rc = XFFT_EDEVICE_INTERNAL;
-    p->n_cut_elements = (int64_t)hc[0];
-    p->n_multilabel = (int64_t)hc[1];
-    const int64_t nirr = g.nirr > 0 ? g.nirr : 1, nX = g.nX > 0 ? g.nX : 1;
     if (!rc) {
-        if (hipMalloc(&p->irr_j, sizeof(int32_t) * 8 * nirr) != hipSuccess ||
-            hipMalloc(&p->irr_lab, sizeof(int32_t) * 12 * nirr) != hipSuccess ||
-            hipMalloc(&p->t64.irr_L, sizeof(double) * 8 * nirr) != hipSuccess ||
-            hipMalloc(&p->t32.irr_L, sizeof(float) * 8 * nirr) != hipSuccess ||
-            hipMalloc(&p->irr_node, sizeof(int32_t) * 8 * nirr) != hipSuccess ||
-            hipMalloc(&p->d0, sizeof(double) * nX) != hipSuccess ||
-            hipMalloc(&p->t64.d0is, sizeof(double) * nX) != hipSuccess ||
-            hipMalloc(&p->t32.d0is, sizeof(float) * nX) != hipSuccess ||
-            hipMalloc(&p->enr_src, sizeof(int32_t) * 8 * nX) != hipSuccess)
-            rc = XFFT_ENOMEM_INTERNAL;
+        k_snap<<<blocks(N), tb, 0, s>>>(N, L_dev_raw, 1.0 / p->h, p->snap_eps, p->phase, g.nphase, p->Ls, &cnt->err);
+        k_classify<<<blocks(N), tb, 0, s>>>(g.n0, g.n1, g.n2, p->Ls, p->phase, p->p1, vflag, vlab, jflag,
+                                            cnt->elements);
+        scan_flags(s, N, vflag, sc[0], so[0], &cnt->irregular);
+        scan_flags(s, N, jflag, sc[1], so[1], &cnt->enriched);
+        fetch();
     }
-    if (!rc && g.nirr > 0) {
-        k_irr_tables<<<(unsigned)((g.nirr + tb - 1) / tb), tb, 0, s>>>(g.nirr, g.n0, g.n1, g.n2, p->irr, p->Ls,
-                                                                       p->phase, jmap, p->irr_j, p->irr_lab,
-                                                                       p->t64.irr_L, p->t32.irr_L);
-        rc = element_lists(p);
+    if (!rc && h.err) rc = XFFT_EINVAL_INTERNAL;
+    if (!rc) {
+        g.nirr = h.irregular;
+        g.nX = h.enriched;
+        p->n_cut_elements = (int64_t)h.elements[0];
+        p->n_multilabel = (int64_t)h.elements[1];
     }
-    if (!rc && g.nX > 0) {
-        k_d0<<<(unsigned)((g.nX + tb - 1) / tb), tb, 0, s>>>(g.nX, g.n0, g.n1, g.n2, p->jlist, p->vmat, p->t64.irr_L,
-                                                             g.nirr, p->d0_scale, p->d0, p->t64.d0is, p->t32.d0is);
-        k_enr_src<<<(unsigned)((g.nX + tb - 1) / tb), tb, 0, s>>>(g.nX, g.n0, g.n1, g.n2, p->jlist, p->vmat,
-                                                                  p->enr_src);
+    const int64_t nirr = g.nirr, nX = g.nX, nc = p->n_cut_elements, nu = 6 * nirr - nc;
+    const int nblk = (int)((nirr + IRR_VB - 1) / IRR_VB);
+    if (!rc && !carve(&p->geom_block, [&](Carve &c) {
+            c.take(p->irr, nirr);
+            c.take(p->jlist, nX);
+            c.take(p->irr_j, 8 * nirr);
+            c.take(p->irr_node, 8 * nirr);
+            c.take(p->irr_lab, 12 * nirr);
+            c.take(p->t64.irr_L, 8 * nirr);
+            c.take(p->t32.irr_L, 8 * nirr);
+            c.take(p->tet_cut, nc);
+            c.take(p->tet_uncut, nu);
+            c.take(p->cut_pos, 6 * nirr);
+            c.take(p->blk_cut, nblk + 1);
+            c.take(p->cut_lab, 2 * nc);
+            c.take(p->uncut_lab, nu);
+            c.take(p->t64.cut_M, 10 * nc);
+            c.take(p->t32.cut_M, 10 * nc);
+            c.take(p->d0, nX);
+            c.take(p->t64.d0is, nX);
+            c.take(p->t32.d0is, nX);
+            c.take(p->enr_src, 8 * nX);
+        }))
+        rc = XFFT_ENOMEM_INTERNAL;
+    if (!rc) {
+        emit_lists(s, N, vflag, so[0], p->irr, p->vmat, vlab, nullptr);
+        emit_lists(s, N, jflag, so[1], p->jlist, jmap, nullptr, nullptr);
     }
-    if (!rc && hipStreamSynchronize(s) != hipSuccess) rc = XFFT_EDEVICE_INTERNAL;
-    if (!rc && hipGetLastError() != hipSuccess) rc = XFFT_EDEVICE_INTERNAL;
-    cleanup();
+    if (!rc && nirr > 0) {
+        k_irr_tables<<<blocks(nirr), tb, 0, s>>>(nirr, g.n0, g.n1, g.n2, p->irr, p->Ls, p->phase, jmap, p->irr_j,
+                                                 p->irr_node, p->irr_lab, p->t64.irr_L, p->t32.irr_L, cut);
+        // lists of the cut and the uncut elements; their lengths are known from the
+        // classification, which decides by the same comparisons
+        scan_flags(s, 6 * nirr, cut, sc[2], so[2], &cnt->cut);
+        emit_lists(s, 6 * nirr, cut, so[2], p->tet_cut, p->cut_pos, nullptr, p->tet_uncut);
+        k_blk_cut<<<(unsigned)((nblk + 256) / 256), 256, 0, s>>>(nblk, nc, p->tet_cut, p->blk_cut);
+        if (nc)
+            k_cut_moments<<<blocks(nc), tb, 0, s>>>(nc, nirr, p->tet_cut, p->t64.irr_L, p->irr_lab, p->t64.cut_M,
+                                                    p->t32.cut_M, p->cut_lab);
+        if (nu) k_uncut_lab<<<blocks(nu), tb, 0, s>>>(nu, nirr, p->tet_uncut, p->irr_lab, p->uncut_lab);
+    }
+    if (!rc && nX > 0) {
+        k_d0<<<blocks(nX), tb, 0, s>>>(nX, g.n0, g.n1, g.n2, p->jlist, p->vmat, p->t64.irr_L, nirr, p->d0_scale, p->d0,
+                                       p->t64.d0is, p->t32.d0is);
+        k_enr_src<<<blocks(nX), tb, 0, s>>>(nX, g.n0, g.n1, g.n2, p->jlist, p->vmat, p->enr_src);
+    }
+    if (!rc) fetch();
+    if (!rc && (hipGetLastError() != hipSuccess || (nirr > 0 && h.cut != nc))) rc = XFFT_EDEVICE_INTERNAL;
+    (void)hipFree(scratch);
     return rc;
 }
 
 int compute_tables(xfft_problem *p) {
     hipStream_t s = p->stream;
     const int n[3] = {p->g.n0, p->g.n1, p->g.n2};
+    const int np = p->g.nphase;
+    const bool plane = fft_variants<double>(p->g) & 1 || fft_variants<float>(p->g) & 1;
+    if (!carve(&p->table_block, [&](Carve &c) {
+            for (int a = 0; a < 3; ++a) {
+                c.take(p->t64.tw[a], n[a]);
+                c.take(p->t32.tw[a], n[a]);
+                c.take(p->t64.half[a], 2 * n[a]);
+                c.take(p->t32.half[a], 2 * n[a]);
+                c.take(p->t64.tws[a], n[a]);
+                c.take(p->t32.tws[a], n[a]);
+            }
+            if (plane) {
+                c.take(p->t64.twp, n[0]);
+                c.take(p->t32.twp, n[0]);
+            }
+            c.take(p->t64.lame, 2 * np);
+            c.take(p->t32.lame, 2 * np);
+        }))
+        return XFFT_ENOMEM_INTERNAL;
     for (int a = 0; a < 3; ++a) {
         p->plan[a] = make_plan(n[a]);
-        if (hipMalloc(&p->t64.tw[a], sizeof(cpx<double>) * n[a]) != hipSuccess ||
-            hipMalloc(&p->t32.tw[a], sizeof(cpx<float>) * n[a]) != hipSuccess ||
-            hipMalloc(&p->t64.half[a], sizeof(double) * 2 * n[a]) != hipSuccess ||
-            hipMalloc(&p->t32.half[a], sizeof(float) * 2 * n[a]) != hipSuccess ||
-            hipMalloc(&p->t64.tws[a], sizeof(cpx<double>) * n[a]) != hipSuccess ||
-            hipMalloc(&p->t32.tws[a], sizeof(cpx<float>) * n[a]) != hipSuccess)
-            return XFFT_ENOMEM_INTERNAL;
-        k_fft_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(n[a], reinterpret_cast<double2 *>(p->t64.tw[a]),
-                                                        reinterpret_cast<float2 *>(p->t32.tw[a]), p->t64.half[a],
-                                                        p->t32.half[a]);
-        k_fft_stage_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(
-            n[a], reinterpret_cast<const double2 *>(p->t64.tw[a]), reinterpret_cast<const float2 *>(p->t32.tw[a]),
-            reinterpret_cast<double2 *>(p->t64.tws[a]), reinterpret_cast<float2 *>(p->t32.tws[a]), false);
-        if (a == 0) {
-            // the xy-plane kernels take the narrow plan in FP64
-            if (hipMalloc(&p->t64.twp, sizeof(cpx<double>) * n[a]) != hipSuccess ||
-                hipMalloc(&p->t32.twp, sizeof(cpx<float>) * n[a]) != hipSuccess)
-                return XFFT_ENOMEM_INTERNAL;
-            k_fft_stage_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(
-                n[a], reinterpret_cast<const double2 *>(p->t64.tw[a]), reinterpret_cast<const float2 *>(p->t32.tw[a]),
-                reinterpret_cast<double2 *>(p->t64.twp), reinterpret_cast<float2 *>(p->t32.twp), true);
-        }
+        const auto c64 = [](cpx<double> *q) { return reinterpret_cast<double2 *>(q); };
+        const auto c32 = [](cpx<float> *q) { return reinterpret_cast<float2 *>(q); };
+        k_fft_tables<<<(n[a] + 255) / 256, 256, 0, s>>>(n[a], c64(p->t64.tw[a]), c32(p->t32.tw[a]), p->t64.half[a],
+                                                        p->t32.half[a], c64(p->t64.tws[a]), c32(p->t32.tws[a]),
+                                                        a == 0 ? c64(p->t64.twp) : nullptr,
+                                                        a == 0 ? c32(p->t32.twp) : nullptr);
     }
-    const int np = p->g.nphase;
-    if (hipMalloc(&p->t64.lame, sizeof(double) * 2 * np) != hipSuccess ||
-        hipMalloc(&p->t32.lame, sizeof(float) * 2 * np) != hipSuccess)
-        return XFFT_ENOMEM_INTERNAL;
     if (hipMemcpyAsync(p->t64.lame, p->lame_host.data(), sizeof(double) * 2 * np, hipMemcpyHostToDevice, s) !=
         hipSuccess)
         return XFFT_EDEVICE_INTERNAL;

@@ -24,6 +24,7 @@ static unsigned g_reg_grid;             /* workgroups of the last regular-voxel 
 static int g_last_regular;              /* the last launch was an operator application */
 static float (*g_elapsed)(void);        /* event time of the launches since the last one, < 0: the call fails */
 static int g_timings;
+static int g_mallocs, g_frees, g_waits, g_launches;
 static int g_device, g_big_launches, g_bad_launches;   /* current device; launches above 64 KB of dynamic LDS */
 
 /* ---------------------------------------------------------------- kernels */
@@ -61,6 +62,7 @@ int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *lds, void **s) {
 }
 int hipLaunchKernel(const void *f, Dim3 grid, Dim3 block, void **args, size_t lds, void *s) {
     (void)block; (void)s;
+    ++g_launches;
     const int k = kernel_index(f);
     const char *n = g_kernels[k].name;
     if (lds > 65536) {
@@ -84,8 +86,8 @@ int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; re
 int hipFuncSetAttribute(const void *f, int a, int v) { (void)a; g_kernels[kernel_index(f)].lds[g_device] = (size_t)v; return 0; }
 int hipGetSymbolAddress(void **p, const void *sym) { (void)sym; *p = calloc(1, (size_t)64 << 20); return *p ? 0 : 2; }
 int hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return 0; }
-int hipMalloc(void **p, size_t n) { *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
-int hipFree(void *p) { free(p); return 0; }
+int hipMalloc(void **p, size_t n) { ++g_mallocs; *p = calloc(1, n ? n : 1); return *p ? 0 : 2; }
+int hipFree(void *p) { ++g_frees; free(p); return 0; }
 int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; return hipMalloc(p, n); }
 int hipHostFree(void *p) { return hipFree(p); }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *q) { (void)k; (void)q; memcpy(d, s, n); return 0; }
@@ -93,7 +95,7 @@ int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n
 int hipMemsetAsync(void *d, int v, size_t n, void *q) { (void)q; memset(d, v, n); return 0; }
 int hipStreamCreate(void **s) { return hipMalloc(s, 1); }
 int hipStreamDestroy(void *s) { return hipFree(s); }
-int hipStreamSynchronize(void *s) { (void)s; return 0; }
+int hipStreamSynchronize(void *s) { ++g_waits; (void)s; return 0; }
 int hipStreamWaitEvent(void *s, void *e, unsigned f) { (void)s; (void)e; (void)f; return 0; }
 int hipEventCreate(void **e) { return hipMalloc(e, 1); }
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; return hipMalloc(e, 1); }
@@ -212,8 +214,26 @@ static void scenario_devices(int n, int precision) {
     }
 }
 
+/* ---------------------------------------------------------------- cost of building a problem
+ * Small grids pay for the calls of the setup, not for its kernels: allocations and
+ * waits of xfft_setup, and frees of the scratch it takes, at most those given. */
+static void scenario_setup(int n0, int n1, int mallocs, int frees, int waits) {
+    g_totals[0] = 100; g_totals[1] = 300; g_totals[2] = 400;
+    make_problem(16, 16, 16, 0, XFFT_FP64);              /* first use of the device */
+    g_mallocs = g_frees = g_waits = g_launches = 0;
+    xfft_problem *p = make_problem(n0, n1, 12, 0, XFFT_FP64);
+    printf("%d allocations, %d frees, %d waits, %d launches\n", g_mallocs, g_frees, g_waits, g_launches);
+    expect(g_mallocs <= mallocs, 1, "allocations of a setup");
+    expect(g_frees <= frees, 1, "frees of a setup");
+    expect(g_waits <= waits, 1, "waits of a setup");
+    xfft_destroy(p);
+    expect(g_mallocs, g_frees, "everything freed with the problem");
+}
+
 int main(int argc, char **argv) {
-    if (argc == 4 && !strcmp(argv[1], "devices")) scenario_devices(atoi(argv[2]), atoi(argv[3]));
+    if (argc == 7 && !strcmp(argv[1], "setup"))
+        scenario_setup(atoi(argv[2]), atoi(argv[3]), atoi(argv[4]), atoi(argv[5]), atoi(argv[6]));
+    else if (argc == 4 && !strcmp(argv[1], "devices")) scenario_devices(atoi(argv[2]), atoi(argv[3]));
     else if (argc == 3 && !strcmp(argv[1], "depth")) scenario_depth(argv[2]);
     else return 2;
     if (g_fail) return 1;

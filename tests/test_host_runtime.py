@@ -9,7 +9,10 @@ code asks for can be counted and the event times of the autotuner scripted:
   decide; a depth that pays is taken and kept for the grid; after a failed
   timing the default stays and the next problem times again;
 * dynamic LDS: on each of two devices of one process, every launch with more
-  than 64 KB follows the attribute that allows it on that device.
+  than 64 KB follows the attribute that allows it on that device;
+* setup: no more allocations, frees and waits than 49, 13 and 8 (those of the
+  library before the lists of cut elements were built at setup), and everything
+  freed with the problem.
 """
 
 import os
@@ -51,3 +54,8 @@ def test_depth_of_the_regular_march(program, case):
 @pytest.mark.parametrize("n,precision", [(128, 0), (96, 1), (108, 0)])
 def test_lds_attribute_on_every_device(program, n, precision):
     _run(program, "devices", str(n), str(precision))
+
+
+@pytest.mark.parametrize("n0,n1", [(16, 16), (24, 18)])
+def test_calls_of_a_setup(program, n0, n1):
+    _run(program, "setup", str(n0), str(n1), "49", "13", "8")
