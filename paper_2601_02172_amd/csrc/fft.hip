@@ -984,25 +984,35 @@ void k_fft_z_t(FftArgs A, const cpx<T> *tw, const T *h0, const T *h1,
 // reads global memory into registers and the last inverse one writes it.  A value
 // crosses LDS twice (4 accesses) with three barriers, instead of 12 accesses and
 // ten barriers in k_fft_z_t.  Lane kl of 16 (8 in FP64) takes column kx0 + kl, so
-// every row of a run is one 128-byte access.  Bound: below 128^3 the chain load -
-// barrier - Green - barrier - store of the few workgroups a CU holds, above it the
-// 128-byte runs.  256 threads also where a stage has fewer items, because the
-// enriched workgroups of the same launch need them (128 threads: 14 us instead of
-// 10 at 64^3 FP64).
+// a row of a run is one access of min(TK, ceil(nh / ntiles)) columns, 88 ... 128
+// bytes (88 at n0 = 64 and 104 at n0 = 128 in FP32), which starts anywhere in the
+// unpadded rows of the xy-plane kernels and where a multiple of the run's width
+// falls in the padded ones.  Bound: below 128^3 the chain load - barrier - Green -
+// barrier - store of the few workgroups a CU holds, above it the short runs.  256
+// threads also where a stage has fewer items, because the enriched workgroups of
+// the same launch need them (128 threads: 14 us instead of 10 at 64^3 FP64).
 constexpr int zp_r1(int n) {
     for (int r1 : {16, 12, 9, 8, 6, 4})
         for (int r2 : {16, 12, 9, 8, 6, 4, 3})
             if (r1 * r2 == n) return r1;
     return 0;
 }
-// Where it is used; us per launch, k_fft_z_t / k_fft_z2.  FP32, 6 loads: up to a
-// middle radix of 6, whose three components fit five waves per SIMD: n2 = 36
-// 12.7 / 11.1, 54 18 / 15.8, 64 21 / 17, 72 26 / 20.6, 96 47.8 / 47.1; above it the
-// registers leave too few waves (128 101 / 104, 256 812 / 1005).  FP64, 1 and 6 loads:
-// from 96 on up to a middle radix of 9 (96 22.4 / 20.5 and 102 / 102, 108 31.3 / 24.4
-// and 139 / 106, 128 40.6 / 37.6 and 238 / 204) and with a first radix of 16 (64
-// 11.8 / 10.0 and 32.4 / 29.8); not at 54 and 72 (6 loads: 46.5 / 55.5 and
-// 46.7 / 49.4), where half the threads have no item in either stage.
+// Where it is used; us per launch on the cube of that size, k_fft_z_t / k_fft_z2.
+// FP32, 1 and 6 loads, up to a middle radix of 6: n2 = 12 7.4 / 7.1 and 7.7 / 7.6,
+// 16 7.6 / 7.1 and 7.9 / 7.6, 18 8.1 / 6.9 and 8.7 / 7.5, 24 8.6 / 7.0 and 9.3 / 7.8,
+// 32 8.0 / 7.3 and 10.1 / 9.1, 36 9.4 / 7.6 and 11.7 / 9.8, 48 10.2 / 8.1 and 15.4 /
+// 11.6, 54 11.1 / 10.1 and 18.3 / 16.0, 64 10.3 / 8.9 and 21.1 / 16.8, 72 13.4 / 11.6
+// and 29.2 / 23.8, 96 15.4 / 14.0 and 48.5 / 47.5.  The line was drawn with five
+// waves per SIMD asked of every length (128 101 / 104, 256 812 / 1005); with the four
+// that middle radices from 6 on get now it would hold beyond it: 108 65.9 / 58.4,
+// 128 103.7 / 96.3, 144 152 / 121.
+// FP64, 1 and 6 loads, with a first radix of 16 and from 96 on up to a middle radix
+// of 9: 48 9.8 / 8.8 and 21.8 / 18.0, 64 11.4 / 10.3 and 30.5 / 27.2, 96 20.1 / 18.4 and
+// 91.6 / 91.9, 108 27.9 / 21.8 and 136 / 104, 128 36.6 / 33.3 and 213 / 182, 144 56.2 /
+// 43.4 and 359 / 251.  Below, where the middle part leaves threads without an item
+// (24 8.5 / 7.8 and 10.5 / 8.9, 36 9.8 / 8.5 and 14.7 / 11.7, 72 16.4 / 14.6 and 45.0 /
+// 42.2), 54 is slower with six loads (24.2 / 25.4), and half tiles are from 32 on
+// (11.8 / 12.4, 36 gains, 54 25.6 / 32.4, 72 46.9 / 62.0).
 template <typename T> constexpr bool zp_two(int n) {
     const int r1 = zp_r1(n);
     if (r1 == 0) return false;
@@ -1012,7 +1022,10 @@ template <typename T, int N2, int TK> struct Z2Cfg {
     static constexpr int R1 = zp_r1(N2) ? zp_r1(N2) : 1, R2 = N2 / R1;
     static constexpr int S1 = 3 * R2 * TK, S2 = R1 * TK;       // items of the outer stages and of the middle part
     static constexpr int NT = 256;
-    static constexpr int WV = sizeof(T) == 4 ? 5 : 1;
+    // waves per SIMD asked for: five cost a middle radix of 6 two spilled registers (54,
+    // 72 and 96 at 16 columns), at the same time (us, 6 loads, 5 / 4 waves: 16.3 / 16.0,
+    // 23.8 / 23.8, 47.0 / 47.3)
+    static constexpr int WV = sizeof(T) == 8 ? 1 : R2 >= 6 ? 4 : 5;
     static constexpr int LS = N2 | 1;
 };
 
