@@ -33,27 +33,16 @@ template <typename T> struct Sym {
     T xx, yy, zz, yz, xz, xy;
 };
 
-template <typename T> __device__ __forceinline__ Sym<T> sym_zero() { return {0, 0, 0, 0, 0, 0}; }
 
 // Start value of a sum: -0 is the exact additive identity (x + (-0) == x for
 // every x, -0 included; +0 is not, since -0 + +0 = +0), so the compiler drops
 // the first addition into an accumulator that starts from it.
 template <typename T> __device__ __forceinline__ constexpr T acc_zero() { return -(T)0; }
-template <typename T> __device__ __forceinline__ Sym<T> sym_acc_zero() {
-    return {acc_zero<T>(), acc_zero<T>(), acc_zero<T>(), acc_zero<T>(), acc_zero<T>(), acc_zero<T>()};
-}
 
 // Mandel 6-vector (11,22,33,sqrt2 23,sqrt2 13,sqrt2 12) -> tensor components
 template <typename T> __device__ __forceinline__ Sym<T> from_mandel(const T *m) {
     const T r = (T)0.70710678118654752440;
     return {m[0], m[1], m[2], m[3] * r, m[4] * r, m[5] * r};
-}
-
-// column p (compile-time) of a symmetric tensor
-template <int P, typename T> __device__ __forceinline__ void col(const Sym<T> &s, T &a, T &b, T &c) {
-    if constexpr (P == 0) { a = s.xx; b = s.xy; c = s.xz; }
-    else if constexpr (P == 1) { a = s.xy; b = s.yy; c = s.yz; }
-    else { a = s.xz; b = s.yz; c = s.zz; }
 }
 
 // 3x3 displacement gradient stored by columns: H[p][i] = d u_i / d x_p
@@ -82,30 +71,9 @@ __device__ __forceinline__ Sym<T> sym_of(const Grad<T> &H) {
 }
 
 template <typename T>
-__device__ __forceinline__ Sym<T> hooke(const Sym<T> &e, T lam, T mu2) {
-    const T tr = lam * (e.xx + e.yy + e.zz);
-    return {tr + mu2 * e.xx, tr + mu2 * e.yy, tr + mu2 * e.zz, mu2 * e.yz, mu2 * e.xz, mu2 * e.xy};
-}
-
-template <typename T>
 __device__ __forceinline__ void sym_axpy(Sym<T> &y, T a, const Sym<T> &x) {
     y.xx += a * x.xx; y.yy += a * x.yy; y.zz += a * x.zz;
     y.yz += a * x.yz; y.xz += a * x.xz; y.xy += a * x.xy;
-}
-
-// f[corner] += sigma g_a for the four vertices of Kuhn tet t (scaled by V beforehand)
-template <int t, typename T>
-__device__ __forceinline__ void kuhn_scatter(const Sym<T> &s, T (&F)[8][3]) {
-    constexpr int p0 = perm_axis(t, 0), p1 = perm_axis(t, 1), p2 = perm_axis(t, 2);
-    constexpr int c0 = tet_corner(t, 0), c1 = tet_corner(t, 1), c2 = tet_corner(t, 2), c3 = tet_corner(t, 3);
-    T a0, b0, d0, a1, b1, d1, a2, b2, d2;
-    col<p0>(s, a0, b0, d0);
-    col<p1>(s, a1, b1, d1);
-    col<p2>(s, a2, b2, d2);
-    F[c0][0] -= a0; F[c0][1] -= b0; F[c0][2] -= d0;
-    F[c1][0] += a0 - a1; F[c1][1] += b0 - b1; F[c1][2] += d0 - d1;
-    F[c2][0] += a1 - a2; F[c2][1] += b1 - b2; F[c2][2] += d1 - d2;
-    F[c3][0] += a2; F[c3][1] += b2; F[c3][2] += d2;
 }
 
 // ------------------------------------------------------------------ moments of the sides

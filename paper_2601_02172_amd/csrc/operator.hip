@@ -194,7 +194,7 @@ __global__ __launch_bounds__(256, ST ? 3 : sizeof(T) == 4 ? 5 : 3) void k_regula
     const int i0 = bx * TO, j0 = by * TO;
     const int k0 = zc * A.kz, k1 = min(k0 + A.kz, A.n2);
     const int n0 = A.n0, n1 = A.n1, n2 = A.n2;
-    const int64_t N = A.N, plane_sz = (int64_t)n0 * n1;
+    const int64_t N = A.N;
     const int a = i0 - 1 + tx, b = j0 - 1 + ty;
     // a tile can wrap more than once around a grid of fewer than TE nodes: full
     // modulo there, one wrap otherwise.

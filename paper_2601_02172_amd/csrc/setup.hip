@@ -437,11 +437,6 @@ __global__ void k_lame(int n, const double *lame, float *lame32) {
     if (t < 2 * n) lame32[t] = (float)lame[t];
 }
 
-#define CK(x)                                 \
-    do {                                      \
-        if ((x) != hipSuccess) return XFFT_EDEVICE_INTERNAL; \
-    } while (0)
-
 constexpr int XFFT_EDEVICE_INTERNAL = -3;
 constexpr int XFFT_ENOMEM_INTERNAL = -2;
 constexpr int XFFT_EINVAL_INTERNAL = -1;
