@@ -852,8 +852,8 @@ void xfft_destroy(xfft_problem *p) {
     if (!p) return;
     (void)hipSetDevice(p->device);
     if (p->stream) (void)hipStreamSynchronize(p->stream);
-    void *ptrs[] = {p->Ls, p->phase, p->vmat, p->geom_block, p->table_block, p->partial, p->scal, p->flags, p->ebar,
-                    p->sum7, p->sol_u, p->sol_ue};
+    void *ptrs[] = {p->Ls, p->phase, p->vmat, p->partial, p->scal, p->flags, p->ebar, p->sum7, p->sol_u, p->sol_ue};
+    for (void *q : p->tables) (void)hipFree(q);
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     drop_graph(p);

@@ -213,9 +213,9 @@ struct xfft_problem {
     int scheme = 0;        // XFFT_LCG, XFFT_NLCG, XFFT_BB or XFFT_BASIC
     int p1 = 0;            // 1: voxel-segmented P1 discretisation (no enrichment)
     // geometry (device); the tables of irregular voxels, their elements and the
-    // enriched nodes (irr ... d0, and irr_L, cut_M, d0is of both precisions) are
-    // parts of geom_block, the FFT and moduli tables parts of table_block
-    void *geom_block = nullptr, *table_block = nullptr;
+    // enriched nodes (irr ... d0, and irr_L, cut_M, d0is of both precisions) and the
+    // FFT and moduli tables are parts of the allocations in tables
+    std::vector<void *> tables;
     double *Ls = nullptr;          // snapped level set, voxel units [N]
     int32_t *phase = nullptr;      // [N]
     int32_t *vmat = nullptr;       // [N] material (>= 0) or -(irregular index + 1)

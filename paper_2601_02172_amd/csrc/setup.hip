@@ -17,6 +17,7 @@
 #include "fft_lines.h"
 
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 namespace xfft {
@@ -456,25 +457,59 @@ void emit_lists(hipStream_t s, int64_t n, const uint8_t *flag, const int32_t *of
     k_scan_emit<<<scan_blocks(n), SCAN_T, 0, s>>>(n, flag, off, list, map, lab, comp);
 }
 
-// Parts of one allocation, each on a 256-byte boundary: laid out without a base
-// first, for the size, then with it.
-struct Carve {
-    unsigned char *base = nullptr;
-    size_t size = 0;
-    template <typename P> void take(P *&ptr, int64_t count) {
-        if (base) ptr = reinterpret_cast<P *>(base + size);
-        size += (sizeof(P) * (size_t)count + 255) & ~(size_t)255;
+// Device memory of several arrays.  The runtime hands out less than 2 MB from chunks
+// that it keeps (1 us, also right after a free), more by a call into the driver each
+// (12 us, up to 250 us for memory that is not at hand, as much for the free): arrays
+// of 2 MB and more share one allocation, the others are packed into allocations of up
+// to 1 MB.  A 24^3 problem (3 MB of tables) built while others live takes 0.52 ms so
+// and 0.75 ms with all of it in one allocation; 128^3 is freed in 0.57 instead of 2.6 ms.
+class DeviceArrays {
+public:
+    template <typename P> void add(P *&ptr, int64_t count) {
+        rq_.push_back({&ptr, (sizeof(P) * (size_t)count + 255) & ~(size_t)255});
     }
+    // false when an allocation fails; what was allocated is in own either way
+    bool allocate(std::vector<void *> &own) {
+        constexpr size_t LARGE = (size_t)2 << 20, PACK = (size_t)1 << 20;
+        std::vector<const Request *> part;
+        size_t size = 0;
+        const auto flush = [&]() {
+            if (part.empty()) return true;
+            void *block = nullptr;
+            if (hipMalloc(&block, size ? size : 1) != hipSuccess) return false;
+            own.push_back(block);
+            size_t at = 0;
+            for (const Request *q : part) {
+                void *v = static_cast<unsigned char *>(block) + at;
+                std::memcpy(q->ptr, &v, sizeof(v));
+                at += q->bytes;
+            }
+            part.clear();
+            size = 0;
+            return true;
+        };
+        for (const Request &q : rq_) {
+            if (q.bytes >= LARGE) continue;
+            if (size + q.bytes > PACK && !flush()) return false;
+            part.push_back(&q);
+            size += q.bytes;
+        }
+        if (!flush()) return false;
+        for (const Request &q : rq_) {
+            if (q.bytes < LARGE) continue;
+            part.push_back(&q);
+            size += q.bytes;
+        }
+        return flush();
+    }
+
+private:
+    struct Request {
+        void *ptr;          // where the pointer goes
+        size_t bytes;
+    };
+    std::vector<Request> rq_;
 };
-template <typename F> bool carve(void **block, F parts) {
-    Carve c;
-    parts(c);
-    if (hipMalloc(block, c.size ? c.size : 1) != hipSuccess) return false;
-    c.base = static_cast<unsigned char *>(*block);
-    c.size = 0;
-    parts(c);
-    return true;
-}
 
 // what the host reads back from a setup, in the order of the kernels that fill it
 struct SetupCounts {
@@ -487,37 +522,39 @@ struct SetupCounts {
 
 // L_dev_raw: device copy of the caller's level set (units of len).
 //
-// A small grid pays for the calls of its setup and not for the kernels: with 62
-// allocations, 17 frees and 10 waits 16^3 took 440 us to build, 64^3 725 us and
-// 128^3 2.4 ms; with 8, 2 and 3 they take 290 us, 570 us and 2.1 ms.  So the
-// scratch, the geometry tables and the FFT tables are one allocation each, and
-// the host waits for the list lengths once and for the end once.
+// A small grid pays for the calls of its setup and not for the kernels, so the host
+// waits for the list lengths once and for the end once, and arrays share
+// allocations.  With 62 allocations, 17 frees, 10 waits and 26 launches 16^3 took
+// 440 us to build, 64^3 750 us and 128^3 2.5 ms, and 24^3 and 64^3 0.68 and 1.85 ms
+// while other problems live; with 9 (16^3), 3, 3 and 21 they take 320 us, 660 us,
+// 2.15 ms, 0.52 and 1.54 ms.
 int run_setup(xfft_problem *p, const double *L_dev_raw) {
     hipStream_t s = p->stream;
     Geometry &g = p->g;
     const int64_t N = g.N;
     const int tb = 256;
     const auto blocks = [&](int64_t n) { return (unsigned)((n + tb - 1) / tb); };
-    // the flags of the elements (6 bytes a voxel, at most) take the place of the
-    // flags and labels of voxels and nodes, which are read for the last time before
     SetupCounts *cnt = nullptr;
-    uint8_t *jflag = nullptr, *vflag = nullptr;
+    uint8_t *jflag = nullptr, *vflag = nullptr, *cut = nullptr;
     int32_t *vlab = nullptr, *jmap = nullptr, *sc[3] = {}, *so[3] = {};
-    const int64_t scan_n[3] = {N, N, 6 * N};
-    void *scratch = nullptr;
-    const auto parts = [&](Carve &c) {
-        c.take(cnt, 1);
-        c.take(jflag, 6 * N);
-        c.take(jmap, N);
+    std::vector<void *> scratch;
+    {
+        DeviceArrays d;
+        const int64_t scan_n[3] = {N, N, 6 * N};
+        d.add(cnt, 1);
         for (int q = 0; q < 3; ++q) {
-            c.take(sc[q], scan_blocks(scan_n[q]));
-            c.take(so[q], scan_blocks(scan_n[q]));
+            d.add(sc[q], scan_blocks(scan_n[q]));
+            d.add(so[q], scan_blocks(scan_n[q]));
         }
-    };
-    if (!carve(&scratch, parts)) return XFFT_ENOMEM_INTERNAL;
-    vflag = jflag + N;
-    vlab = reinterpret_cast<int32_t *>(jflag + 2 * N);      // N is a multiple of 8
-    uint8_t *cut = jflag;
+        d.add(jflag, N);
+        d.add(vflag, N);
+        d.add(vlab, N);
+        d.add(jmap, N);
+        if (!d.allocate(scratch)) {
+            for (void *q : scratch) (void)hipFree(q);
+            return XFFT_ENOMEM_INTERNAL;
+        }
+    }
     int rc = 0;
     SetupCounts h;
     const auto fetch = [&]() {
@@ -544,28 +581,31 @@ int run_setup(xfft_problem *p, const double *L_dev_raw) {
     }
     const int64_t nirr = g.nirr, nX = g.nX, nc = p->n_cut_elements, nu = 6 * nirr - nc;
     const int nblk = (int)((nirr + IRR_VB - 1) / IRR_VB);
-    if (!rc && !carve(&p->geom_block, [&](Carve &c) {
-            c.take(p->irr, nirr);
-            c.take(p->jlist, nX);
-            c.take(p->irr_j, 8 * nirr);
-            c.take(p->irr_node, 8 * nirr);
-            c.take(p->irr_lab, 12 * nirr);
-            c.take(p->t64.irr_L, 8 * nirr);
-            c.take(p->t32.irr_L, 8 * nirr);
-            c.take(p->tet_cut, nc);
-            c.take(p->tet_uncut, nu);
-            c.take(p->cut_pos, 6 * nirr);
-            c.take(p->blk_cut, nblk + 1);
-            c.take(p->cut_lab, 2 * nc);
-            c.take(p->uncut_lab, nu);
-            c.take(p->t64.cut_M, 10 * nc);
-            c.take(p->t32.cut_M, 10 * nc);
-            c.take(p->d0, nX);
-            c.take(p->t64.d0is, nX);
-            c.take(p->t32.d0is, nX);
-            c.take(p->enr_src, 8 * nX);
-        }))
-        rc = XFFT_ENOMEM_INTERNAL;
+    if (!rc) {
+        DeviceArrays d;
+        d.add(p->irr, nirr);
+        d.add(p->jlist, nX);
+        d.add(p->irr_j, 8 * nirr);
+        d.add(p->irr_node, 8 * nirr);
+        d.add(p->irr_lab, 12 * nirr);
+        d.add(p->t64.irr_L, 8 * nirr);
+        d.add(p->t32.irr_L, 8 * nirr);
+        d.add(p->tet_cut, nc);
+        d.add(p->tet_uncut, nu);
+        d.add(p->cut_pos, 6 * nirr);
+        d.add(p->blk_cut, nblk + 1);
+        d.add(p->cut_lab, 2 * nc);
+        d.add(p->uncut_lab, nu);
+        d.add(p->t64.cut_M, 10 * nc);
+        d.add(p->t32.cut_M, 10 * nc);
+        d.add(p->d0, nX);
+        d.add(p->t64.d0is, nX);
+        d.add(p->t32.d0is, nX);
+        d.add(p->enr_src, 8 * nX);
+        DeviceArrays tmp;
+        tmp.add(cut, 6 * nirr);
+        if (!d.allocate(p->tables) || !tmp.allocate(scratch)) rc = XFFT_ENOMEM_INTERNAL;
+    }
     if (!rc) {
         emit_lists(s, N, vflag, so[0], p->irr, p->vmat, vlab, nullptr);
         emit_lists(s, N, jflag, so[1], p->jlist, jmap, nullptr, nullptr);
@@ -590,7 +630,7 @@ int run_setup(xfft_problem *p, const double *L_dev_raw) {
     }
     if (!rc) fetch();
     if (!rc && (hipGetLastError() != hipSuccess || (nirr > 0 && h.cut != nc))) rc = XFFT_EDEVICE_INTERNAL;
-    (void)hipFree(scratch);
+    for (void *q : scratch) (void)hipFree(q);
     return rc;
 }
 
@@ -599,23 +639,22 @@ int compute_tables(xfft_problem *p) {
     const int n[3] = {p->g.n0, p->g.n1, p->g.n2};
     const int np = p->g.nphase;
     const bool plane = fft_variants<double>(p->g) & 1 || fft_variants<float>(p->g) & 1;
-    if (!carve(&p->table_block, [&](Carve &c) {
-            for (int a = 0; a < 3; ++a) {
-                c.take(p->t64.tw[a], n[a]);
-                c.take(p->t32.tw[a], n[a]);
-                c.take(p->t64.half[a], 2 * n[a]);
-                c.take(p->t32.half[a], 2 * n[a]);
-                c.take(p->t64.tws[a], n[a]);
-                c.take(p->t32.tws[a], n[a]);
-            }
-            if (plane) {
-                c.take(p->t64.twp, n[0]);
-                c.take(p->t32.twp, n[0]);
-            }
-            c.take(p->t64.lame, 2 * np);
-            c.take(p->t32.lame, 2 * np);
-        }))
-        return XFFT_ENOMEM_INTERNAL;
+    DeviceArrays d;
+    for (int a = 0; a < 3; ++a) {
+        d.add(p->t64.tw[a], n[a]);
+        d.add(p->t32.tw[a], n[a]);
+        d.add(p->t64.half[a], 2 * n[a]);
+        d.add(p->t32.half[a], 2 * n[a]);
+        d.add(p->t64.tws[a], n[a]);
+        d.add(p->t32.tws[a], n[a]);
+    }
+    if (plane) {
+        d.add(p->t64.twp, n[0]);
+        d.add(p->t32.twp, n[0]);
+    }
+    d.add(p->t64.lame, 2 * np);
+    d.add(p->t32.lame, 2 * np);
+    if (!d.allocate(p->tables)) return XFFT_ENOMEM_INTERNAL;
     for (int a = 0; a < 3; ++a) {
         p->plan[a] = make_plan(n[a]);
         const auto c64 = [](cpx<double> *q) { return reinterpret_cast<double2 *>(q); };
