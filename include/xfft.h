@@ -242,8 +242,9 @@ int xfft_voxel_stress(xfft_problem *p, const double *x, const double *macro_stra
  * the outputs are ready when the stream reaches this point.  The per-workgroup
  * partial sums and the corner-force buffer of the irregular voxels live in a
  * static 64 MiB device array per GPU (held until the process ends), so the call
- * makes no allocation; grids needing more (8 NPART nslots + 384 x irregular
- * voxels bytes, about 150 k irregular voxels) give XFFT_EINVAL, as does a call
+ * makes no allocation; grids needing more (64 bytes per workgroup of an operator
+ * application + 384 x irregular voxels bytes, about 170 k irregular voxels) give
+ * XFFT_EINVAL, as does a call
  * between xfft_profile_begin and xfft_profile_end.  All calls on one GPU share
  * that array: calls that overlap in time on one GPU (other streams, other
  * threads, other problems) race and must be serialised by the caller.
@@ -268,7 +269,7 @@ int xfft_get_layout(xfft_problem *p, int64_t *info, int64_t *jlist, double *d0);
  * that runs inside another class's launch is timed there and its own class
  * counts no launches: the enriched gather always (class 1), the enriched
  * residual with the compile-time z pass (class 5), the enriched CG update with
- * the xy-plane kernels (class 7).
+ * the xy-plane kernels and with the compile-time x pass (class 7).
  * precision: XFFT_FP64 or XFFT_FP32.  Overwrites the problem's work fields. */
 int xfft_profile(xfft_problem *p, int32_t precision, int32_t nrhs, int32_t nrep, double *ms_out,
                  int32_t *count_out);

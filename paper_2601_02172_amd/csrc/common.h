@@ -61,7 +61,7 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t b, int64_t nb) {
 struct FftPlan {
     int n;            // line length
     int nstages;
-    int radix[16];    // radices applied in order (4, 2, 3)
+    int radix[16];    // radices of the run-time plan, applied in order (4, 2, 3)
 };
 FftPlan make_plan(int n);
 

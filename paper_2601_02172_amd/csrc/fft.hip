@@ -7,7 +7,10 @@
 //              A11^0, Parseval partial of f^T G f, inverse FFT along z;
 //   y inverse;
 //   x inverse  c2r of row pairs fused with the CG update of d and u.
-// Every line FFT is an LDS Stockham autosort transform with radices 4, 2, 3.
+// Every line FFT is an LDS Stockham autosort transform: with compile-time plans
+// (radices 16 ... 2, fft_lines.h) for the lengths of FFT_LENGTHS, whose x and y
+// passes are one kernel where a plane fits in LDS, else with plans read at run
+// time (radices 4, 2, 3).
 //
 // Symbol (derived from eq. GreenHermitian for the six Kuhn elements of the
 // reference voxel, identity material; real and symmetric): with
@@ -1241,7 +1244,7 @@ template <typename T> static void set_spec_layout(const xfft_problem *p, FftArgs
 // kx columns per z-pass workgroup: 3 x TK lines of n2 complex values in LDS
 // (about 50 KB, three workgroups per CU)
 template <typename T> static constexpr int tkz_t(int n2) { return (sizeof(T) == 8 ? 8 : 16) / (n2 > 144 ? 2 : 1); }
-// the alternative tile: twice the columns at n2 = 256 (128-byte runs in FP32,
+// the alternative tile: twice the columns for n2 above 144 (128-byte runs in FP32,
 // one or two workgroups per CU), half of them below (more workgroups per CU)
 template <typename T> static constexpr int tkz_alt(int n2) { return n2 > 144 ? 2 * tkz_t<T>(n2) : tkz_t<T>(n2) / 2; }
 

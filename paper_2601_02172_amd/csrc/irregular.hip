@@ -10,9 +10,10 @@
 // the vertex forces of every element in LDS and sums them per corner in element
 // order (no atomics).
 //
-// Bound by: vector issue (about 850 instructions per wave, 870 per voxel and
-// load) and the gathers of the corner values (22 cache-line accesses per wave
-// load).  One thread per voxel looping over its six elements, the form before,
+// Bound by: vector issue (about 890 instructions per wave with an active load, 85
+// per voxel and load: at full rate 59 of 102 us at 128^3 FP32 with six loads) and
+// latency, the gathers of the corner values (22 cache-line accesses per wave load)
+// above all: its waves wait for 61 % of their time.  One thread per voxel looping over its six elements, the form before,
 // held the 96 corner values and sums in registers (211 VGPRs in FP32, 256 + 158
 // AGPRs in FP64: two and one waves per SIMD), ran the cut path for uncut elements
 // too and chained six elements' loads.  Per launch, before -> now: 128^3 FP32
@@ -215,8 +216,9 @@ template <typename T> struct IrrArgs {
     int blocks;               // workgroups per right-hand side
 };
 
-// Odd strides per voxel and element: lanes of neighbouring voxels and elements
-// fall on different banks.
+// Odd strides per voxel and element: the same place of neighbouring voxels falls on
+// different banks.  Lanes at different corners and elements still meet: 2.4 conflict
+// cycles per LDS instruction, about 14 of 102 us at 128^3 FP32 with six loads.
 constexpr int IN_S = 51, OUT_T = 25, OUT_S = 6 * OUT_T + 1, L_S = 9;
 constexpr int CS_S = 25;          // corner sums, FE and enriched halves: 2 x 25 values in place of a voxel's corner values
 static_assert(2 * CS_S <= IN_S, "the corner sums fit in the place of the corner values");

@@ -18,7 +18,7 @@ template <typename K> inline void allow_lds(std::atomic<uint64_t> &done, int dev
 }
 
 SlotLayout slot_layout(const Geometry &g);
-// regular-voxel operator depth (planes per block); kz in {4, 8, 16}
+// regular-voxel operator depth (planes per block); kz in {4, 8, 16, 32}
 void set_depth(SlotLayout &L, const Geometry &g, int kz);
 int green_slots(const Geometry &g);
 // false when a line FFT of the grid would exceed what the generic passes handle

@@ -160,9 +160,10 @@ __device__ __forceinline__ double dpp_row_shr1(double v) {
 // with the same base when tx, ty >= 1.  Node (a, b) collects corner c of the
 // voxels (a - dx, b - dy): corners 0/4 from its own voxel, 1/5 from the thread
 // at tx - 1, 2/6 from ty - 1 and 3/7 from (tx - 1, ty - 1).
-// Bound in FP32: vector issue, 240 instructions a layer and wave of which the six
-// elements need 210; five waves per SIMD.  Six (the LATE march below, 78
-// registers) were not faster: inside solves, six loads, 128^3 169.3 -> 172.8 us,
+// Bound in FP32: half by vector issue (240 instructions a layer and wave, of which
+// the six elements need 210: at full rate 93 of 168 us at 128^3 with six loads),
+// half by latency (its waves wait for 60 % of their time) at five waves per SIMD.
+// Six (the LATE march below, 78 registers) were not faster: inside solves, six loads, 128^3 169.3 -> 172.8 us,
 // 96^3 71.4 -> 66.8, 256^3 1182 -> 1200.  FP64: latency, so three workgroups a CU
 // instead of two: 46 KB of LDS (row sums in two buffers instead of three) and at
 // most 168 registers (the stress from the finished edge forces, and one plane
@@ -230,8 +231,8 @@ __global__ __launch_bounds__(256, ST ? 3 : sizeof(T) == 4 ? 5 : 3) void k_regula
     // Plane loads go through a ring of three register buffers: the loads of
     // plane kl + 3 are in flight while layer kl is computed and plane kl + 2
     // (loaded one layer earlier) is stored to LDS.  The march is unrolled by
-    // three layers, so LDS slots, register buffers and exchange buffers are
-    // compile-time indices.  LATE: one register buffer, whose next loads are issued
+    // three layers, so plane slots in LDS and register buffers are compile-time
+    // indices; the two row-sum buffers follow the parity of the layer.  LATE: one register buffer, whose next loads are issued
     // when it has been stored, one layer before they are used; the 24 registers
     // this saves are what the FP64 kernel with stress has to save for three waves
     // per SIMD (186 registers with the ring, 24 of them spilled at 168).
